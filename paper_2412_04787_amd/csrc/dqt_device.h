@@ -108,6 +108,21 @@ __device__ __forceinline__ float code_to_f32(uint32_t code) {
   return (float)((int)code - 1);
 }
 
+// 16 packed ternary codes (code q + 1 at bits 2k, 2k+1) -> 16 operand bytes
+// in k order, via the byte lookup `lut` (code 0, 1, 2 -> lut bytes 0, 1, 2):
+// split the four codes of every byte into four byte planes, transpose the
+// 4 x 4 byte matrix, then look each code up.
+__device__ __forceinline__ i32x4 expand16(uint32_t x, uint32_t lut) {
+  const uint32_t e = x & 0x03030303u, f = (x >> 2) & 0x03030303u;
+  const uint32_t g = (x >> 4) & 0x03030303u, h = (x >> 6) & 0x03030303u;
+  const uint32_t efl = __builtin_amdgcn_perm(f, e, 0x05010400u), efh = __builtin_amdgcn_perm(f, e, 0x07030602u);
+  const uint32_t ghl = __builtin_amdgcn_perm(h, g, 0x05010400u), ghh = __builtin_amdgcn_perm(h, g, 0x07030602u);
+  const uint32_t d0 = __builtin_amdgcn_perm(ghl, efl, 0x05040100u), d1 = __builtin_amdgcn_perm(ghl, efl, 0x07060302u);
+  const uint32_t d2 = __builtin_amdgcn_perm(ghh, efh, 0x05040100u), d3 = __builtin_amdgcn_perm(ghh, efh, 0x07060302u);
+  return i32x4{(int)__builtin_amdgcn_perm(0u, lut, d0), (int)__builtin_amdgcn_perm(0u, lut, d1),
+               (int)__builtin_amdgcn_perm(0u, lut, d2), (int)__builtin_amdgcn_perm(0u, lut, d3)};
+}
+
 // ---------------------------------------------------------------- LDS DMA
 using lds_u8 = __attribute__((address_space(3))) uint8_t;
 // One direct-to-LDS load per lane (global_load_lds_dwordx4: 16 bytes, or

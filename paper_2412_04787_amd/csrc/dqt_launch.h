@@ -156,6 +156,17 @@ hipError_t launch_unpack_int4(const void* src, int8_t* dst, int64_t n, hipStream
 hipError_t launch_unpack_int3(const void* src, int8_t* dst, int64_t n, hipStream_t stream);
 hipError_t launch_fwd_batch(const BatchCfg& c, const LinearIO* io, uint8_t* ws, size_t ws_bytes,
                            hipStream_t stream);
+// The forward for few tokens, from the packed codes and without a workspace
+// (fwd_small.hip; the rule with its measurements stands there): a streaming
+// kernel up to kSkinnyM tokens; 128 x 128 tiles above, with the reduction in
+// two halves up to kMidSplitM tokens.
+constexpr int64_t kSkinnyM = 48;
+constexpr int64_t kMidSplitM = 256;
+constexpr int64_t kMidMaxE4M3 = 800;    // tokens
+constexpr int64_t kMidMaxTiles = 512;   // 256 x 256 output tiles of the batch
+constexpr int64_t kMidMaxTiles8 = 384;  // ... with 8-bit codes
+bool fwd_small_applies(const BatchCfg& c, const LinearIO* io);
+hipError_t launch_fwd_small(const BatchCfg& c, const LinearIO* io, hipStream_t stream);
 BwdPlan plan_bwd_batch(int n, const LinearIO* io, int64_t M);
 hipError_t launch_dx_batch(const BatchCfg& c, const LinearIO* io, uint8_t* ws, const BwdPlan& P,
                            hipStream_t stream);

@@ -136,20 +136,6 @@ __device__ __forceinline__ u32x2 tr_read(const lds_u8* base, int off) {
 __device__ __forceinline__ i32x4 join(u32x2 lo, u32x2 hi) {
   return i32x4{(int)lo[0], (int)lo[1], (int)hi[0], (int)hi[1]};
 }
-// 16 packed ternary codes (code q + 1 at bits 2k, 2k+1) -> 16 operand bytes
-// in k order, via the byte lookup `lut` (code 0, 1, 2 -> lut bytes 0, 1, 2):
-// split the four codes of every byte into four byte planes, transpose the
-// 4 x 4 byte matrix, then look each code up.
-__device__ __forceinline__ i32x4 expand16(uint32_t x, uint32_t lut) {
-  const uint32_t e = x & 0x03030303u, f = (x >> 2) & 0x03030303u;
-  const uint32_t g = (x >> 4) & 0x03030303u, h = (x >> 6) & 0x03030303u;
-  const uint32_t efl = __builtin_amdgcn_perm(f, e, 0x05010400u), efh = __builtin_amdgcn_perm(f, e, 0x07030602u);
-  const uint32_t ghl = __builtin_amdgcn_perm(h, g, 0x05010400u), ghh = __builtin_amdgcn_perm(h, g, 0x07030602u);
-  const uint32_t d0 = __builtin_amdgcn_perm(ghl, efl, 0x05040100u), d1 = __builtin_amdgcn_perm(ghl, efl, 0x07060302u);
-  const uint32_t d2 = __builtin_amdgcn_perm(ghh, efh, 0x05040100u), d3 = __builtin_amdgcn_perm(ghh, efh, 0x07060302u);
-  return i32x4{(int)__builtin_amdgcn_perm(0u, lut, d0), (int)__builtin_amdgcn_perm(0u, lut, d1),
-               (int)__builtin_amdgcn_perm(0u, lut, d2), (int)__builtin_amdgcn_perm(0u, lut, d3)};
-}
 // 16 packed ternary codes (code q + 1 at bits 2k) -> 16 FP4 (E2M1) values,
 // value k in nibble k of the 64-bit result (low nibble of each byte first):
 // q = -1 -> 0xA (-1.0), 0 -> 0x0, +1 -> 0x2 (+1.0).  Each 8-code half: its
@@ -1639,6 +1625,7 @@ size_t fwd_batch_workspace_min(int n, const LinearIO* io, int cf) {
 hipError_t launch_fwd_batch(const BatchCfg& c, const LinearIO* io, uint8_t* ws, size_t ws_bytes,
                            hipStream_t stream) {
   if (c.M == 0 || c.n == 0) return hipSuccess;
+  if (fwd_small_applies(c, io)) return launch_fwd_small(c, io, stream);
   LaunchStatus st;
   size_t offs[kMaxBatch];
   const size_t full =
