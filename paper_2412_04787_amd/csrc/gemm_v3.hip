@@ -13,7 +13,23 @@
 //    (global_load_lds_dwordx4, no VGPR staging) in steps of one 128-byte
 //    cache line per tile row (128 int8 / e4m3 or 64 bf16 reduction
 //    elements): streaming whole lines delivers ~35 B/clk/CU, half lines only
-//    ~21.  Two 64 KB stages: the DMA of step s+1 lands while step s runs.
+//    ~21.  Two stages of 64 KB.  A copy's address is a wave-uniform base in
+//    scalar registers plus one 32-bit offset per lane.
+//  * Two-phase loop: a step is four quarters of the wave's outputs, each a
+//    memory part (fragment reads, then the copies of one half-tile of a
+//    later step) and a compute part (8 matrix instructions); the two waves
+//    of a SIMD run half a phase apart, so one's memory part always runs
+//    beside the other's matrix instructions, and five half-tiles of copies
+//    stay in flight.  Bound by the board's power: the matrix cores are busy
+//    79 % of the cycles (60 % with all waves in the same phase and the copies
+//    in one burst per step), and the clock falls from 1.87 to about 1.6 GHz
+//    under it.  Measured, that form -> this: hidden-4096 backward + SR 5.85
+//    -> 5.06 ms (1310 TFLOP/s), hidden-2048 3.05 -> 2.70 ms, hidden-768 282
+//    -> 263 us; forward hidden-4096 (FP4 x e4m3) 1.41 -> 1.30 ms, hidden-2048
+//    int8 908 -> 863 us.  Of that, moving the copies behind the fragment
+//    reads gave 4 %, scalar base addresses 8 % (64-bit vector addresses cost
+//    issue slots and registers), reading one half-tile of B a step early 1.5
+//    %; raised wave priority in the compute part cost 0.5 %.
 //  * Persistent grid, one block per CU.  XCD x (workgroups are dispatched
 //    round-robin over the 8 XCDs, each with its own L2) owns a contiguous
 //    1/8 of every problem's tiles, problems sorted longest reduction first;
@@ -48,37 +64,27 @@ namespace v3 {
 
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
-#ifndef GEMM_NW
-#define GEMM_NW 8
-#endif
-constexpr int NW = GEMM_NW;           // waves per block: 8 (2 x 4 grid) or 4 (2 x 2)
-static_assert(NW == 8 || NW == 4, "8 or 4 waves");
+constexpr int NW = 8;                 // waves per block: a 2 x 4 grid
 constexpr int NTH = 64 * NW;
 constexpr int NTD = NTH;             // threads issuing global -> LDS copies
 constexpr int TILE = 256;             // block tile edge (outputs)
 constexpr int WI = 4;                 // MFMA 32x32 blocks per wave along rows
-constexpr int WJ = NW == 8 ? 2 : 4;   // ... and along columns
+constexpr int WJ = 2;                 // ... and along columns
 constexpr int WGC = TILE / (32 * WJ); // waves per row of the wave grid
-// packed ternary codes per tile row per step: one code per reduction element,
-// four per byte (32 bytes for an 8-bit step of 128, 16 for a bf16 step of 64)
-template <int KB, int EB>
-constexpr int pkb() { return KB / EB / 4; }
-
-// Step geometry for KB reduction bytes per tile row per step (128: one cache
-// line; 64: half a line, used with more stages in flight).  K-contiguous
-// tiles are [256 rows][KB bytes]; K-major (bf16) tiles are KB / 2 reduction
-// rows of 256 columns, stored as four 64-column regions.
-template <int KB>
+// Step geometry: KB reduction bytes per tile row per step (one cache line).
+// K-contiguous tiles are [256 rows][KB bytes]; K-major (bf16) tiles are KR
+// reduction rows of 256 columns, stored as four 64-column regions.  Packed
+// ternary codes are PKB bytes per row per step (four codes a byte).
+constexpr int KB = 128;
+constexpr int PKB = KB / 4;
 struct Geo {
-  static_assert(KB == 128 || KB == 64, "step of 64 or 128 bytes");
   static constexpr int OPB = TILE * KB;       // bytes per operand per stage
-  static constexpr int NL = OPB / 16 / NTD;   // DMA chunks per DMA thread per operand
+  static constexpr int NL = OPB / 16 / NTD;   // DMA chunks per thread per operand
   static constexpr int CPR = KB / 16;         // K-contiguous 16-byte chunks per row
   static constexpr int KR = KB / 2;           // K-major rows per step
-  static constexpr int NKK = KB / 32;         // MFMA sub-steps per step
   // K-contiguous swizzle: chunk c of row r sits at c ^ swz(r) (conflict-free
-  // ds_read_b128 for 8 or 4 chunks per row)
-  __device__ static int swz(int r) { return CPR == 8 ? (r >> 1) & 7 : (r >> 2) & 3; }
+  // ds_read_b128)
+  __device__ static int swz(int r) { return (r >> 1) & 7; }
 };
 
 
@@ -90,11 +96,9 @@ enum Elem { EI8 = 0, EF8 = 1, EBF16 = 2, EF4B = 3 };
 // by a pass into the workspace
 enum Mode { KC = 0, KM = 1, KCP = 2, KF4 = 3 };
 
-// bytes per stage: A, then B (bf16 / 8-bit operand, or packed ternary codes)
-template <int MB, int KB, int EB>
-constexpr int slot_bytes() {
-  return Geo<KB>::OPB + (MB == KCP ? TILE * pkb<KB, EB>() : MB == KF4 ? TILE * KB / 2 : Geo<KB>::OPB);
-}
+// bytes per stage: A, then B (bf16 / 8-bit operand, FP4 values or packed codes)
+template <int MB>
+constexpr int slot_bytes() { return Geo::OPB + (MB == KCP ? TILE * PKB : MB == KF4 ? TILE * KB / 2 : Geo::OPB); }
 
 
 // Global operand: base of element (row 0, reduction 0), row stride in bytes,
@@ -168,56 +172,36 @@ __device__ __forceinline__ int opaque(int x) {
   return x;
 }
 
-// Per-thread DMA plan of one operand of one tile: the global address of each
-// of its NL chunks at step 0; the reduction offset (elements, within a step)
-// the chunks cover, which is the same for all of them; and the distance
-// back from a chunk's address to a safe one in the same row (K-contiguous)
-// or column (K-major) for loads past the end of the reduction.
-template <int MODE, int EB, int KB>
+// Per-thread DMA plan of one operand of one tile (the loop for packed codes):
+// the global address of each of its NL chunks at step 0; the reduction offset
+// (elements, within a step) the chunks cover, which is the same for all of
+// them; and the distance back from a chunk's address to a safe one in the
+// same row for loads past the end of the reduction.
+template <int MODE, int EB>
 struct Plan {
-  using G = Geo<KB>;
-  static constexpr int PK = pkb<KB, EB>();
-  static constexpr int CH = TILE * PK / 16;   // packed 16-byte chunks per stage
-  // packed codes: all threads (32-byte rows), or the first CH threads (16-byte rows)
-  static constexpr int NL = MODE == KCP ? (CH >= NTD ? CH / NTD : 1) : MODE == KF4 ? G::NL / 2 : G::NL;
-  // K-major: a thread's chunks cover two reduction rows, k and k + KSTEP,
-  // when one wave instruction's 8 rows repeat within a region (4 waves)
-  static constexpr int KSTEP = MODE == KM && NTD < G::KR * 8 ? NTD / 8 : 0;
-  static_assert(KSTEP == 0 || G::KR * 8 == 2 * NTD, "K-major chunks cover at most two reduction rows");
+  using G = Geo;
+  static constexpr int CH = TILE * PKB / 16;   // packed 16-byte chunks per stage
+  static constexpr int NL = MODE == KCP ? CH / NTD : G::NL;
+  static_assert(CH % NTD == 0, "every thread copies packed codes");
   const uint8_t* g[NL];
   int64_t back;
   int64_t inc;
   int rk;
-  // reduction offset of chunk q (elements within the step) and the distance
-  // back from it to a safe address
-  __device__ int rk_of(int q) const { return rk + (KSTEP && (q & 1) ? KSTEP : 0); }
-  __device__ int64_t back_of(int q, int64_t ld) const { return back + (KSTEP && (q & 1) ? KSTEP * ld : 0); }
 
   __device__ void init(const Opnd& o, int64_t row0, int64_t r_begin, int tid) {
 #pragma unroll
     for (int q = 0; q < NL; ++q) {
       const int p = q * NTD + tid;                  // physical 16-byte position
       if constexpr (MODE == KCP) {
-        // 32-byte rows: two chunks, swapped on odd groups of 8 rows; 16-byte
-        // rows (bf16 steps): one chunk, whose halves the packing arranges
-        const int row = PK == 32 ? p >> 1 : p;
-        const int c = PK == 32 ? (p & 1) ^ ((row >> 3) & 1) : 0;   // logical 16-byte chunk (64 codes)
+        // 32-byte rows: two chunks of 64 codes, swapped on odd groups of 8 rows
+        const int row = p >> 1;
+        const int c = (p & 1) ^ ((row >> 3) & 1);
         int64_t gr = row0 + row;
         if (gr > o.n - 1) gr = o.n - 1;
         g[q] = o.p + gr * o.ld + r_begin / 4 + 16 * c;
         back = r_begin / 4 + 16 * c;
         rk = 64 * c;
-      } else if constexpr (MODE == KF4) {
-        // rows of KB / 2 bytes (4 chunks of 32 values), chunk c of row r at
-        // position c ^ ((r >> 2) & 3): conflict-free 16-byte reads
-        const int row = p >> 2;
-        const int c = (p & 3) ^ ((row >> 2) & 3);
-        int64_t gr = row0 + row;
-        if (gr > o.n - 1) gr = o.n - 1;
-        g[q] = o.p + gr * o.ld + r_begin / 2 + 16 * c;
-        back = r_begin / 2 + 16 * c;
-        rk = 32 * c;
-      } else if constexpr (MODE == KC) {
+      } else {
         const int row = p / G::CPR;
         const int c = (p % G::CPR) ^ G::swz(row);   // logical chunk (same for every q)
         int64_t gr = row0 + row;
@@ -225,22 +209,75 @@ struct Plan {
         g[q] = o.p + gr * o.ld + r_begin * EB + 16 * c;
         back = r_begin * EB + 16 * c;
         rk = 16 * c / EB;
-      } else {
-        const int region = p / (G::KR * 8);         // 64-column region
-        const int k = (p % (G::KR * 8)) >> 3;       // reduction row within the step
-        const int pc = p & 7;
-        const int seg = (pc >> 1) ^ (k & 3);
-        int64_t col = row0 + 64 * region + 16 * seg + 8 * (pc & 1);
-        if (col > o.n - 8) col = o.n - 8;
-        g[q] = o.p + (r_begin + k) * o.ld + 2 * col;
-        if (q == 0) {                               // chunks q > 0: rk_of / back_of
-          back = (int64_t)k * o.ld;
-          rk = k;
-        }
       }
     }
-    inc = MODE == KC ? KB : MODE == KCP ? PK : MODE == KF4 ? KB / 2 : G::KR * o.ld;
+    inc = MODE == KC ? KB : PKB;
   }
+};
+
+// Copy plan of one operand of the two-phase loop (kPP): a wave's copy q
+// moves 8 rows (K-contiguous; 8 reduction rows of 64 columns when K-major) of
+// 128 bytes, so its address is a wave-uniform base, kept in scalar registers,
+// plus a 32-bit offset per lane, within 8 rows.  B32: copies q = 2 j + u
+// cover the rows whose bit 5 is j (the waves' column block j); such an
+// operand's rows are weights' rows, a multiple of 16, so a copy's rows are
+// all inside or all outside and one offset serves every copy.
+template <int MODE, int EB, bool B32>
+struct PPlan {
+  static_assert(MODE == KC || MODE == KM || (MODE == KF4 && B32), "operands of the two-phase loop");
+  static constexpr int NV = B32 && MODE != KM ? 1 : 4;
+  static constexpr int NB = MODE == KC ? 4 : MODE == KF4 ? 2 : 1;
+  const uint8_t* b[NB];
+  int64_t inc;
+  uint32_t vo[NV];
+  __device__ static int row_of(int q, int w) {       // first row of copy q of wave w
+    return B32 ? 64 * (2 * (q & 1) + (w >> 2)) + 32 * (q >> 1) + 8 * (w & 3) : 64 * q + 8 * w;
+  }
+  // position of this lane's 16 bytes in its row (K-contiguous) and its row
+  __device__ static int chunk(int w, int lane) { return (lane & 7) ^ Geo::swz(8 * w + (lane >> 3)); }
+  // first row (K-contiguous) of copy q, inside the operand
+  __device__ static int64_t first_row(const Opnd& o, int64_t row0, int q, int w) {
+    const int64_t gr = row0 + (MODE == KF4 ? 64 * (w >> 1) + 32 * q + 16 * (w & 1) : row_of(q, w));
+    const int64_t last = MODE == KF4 ? o.n - 16 : B32 ? o.n - 8 : o.n - 1;
+    return gr < last ? gr : last;
+  }
+  // this lane's distance from copy q's base
+  __device__ static int64_t lane_off(const Opnd& o, int64_t row0, int q, int w, int lane) {
+    if constexpr (MODE == KC) {
+      const int64_t rest = o.n - 1 - first_row(o, row0, q, w);   // rows of the copy past its first
+      const int64_t r = B32 || (lane >> 3) < rest ? lane >> 3 : rest;
+      return r * o.ld + 16 * chunk(w, lane);
+    } else if constexpr (MODE == KF4) {
+      // rows of 64 bytes: copy j moves 16 rows of the waves' column block j
+      return (lane >> 2) * o.ld + 16 * chunk4(lane);
+    } else {
+      const int pc = lane & 7, k = lane >> 3;
+      int64_t col = row0 + 64 * q + 16 * ((pc >> 1) ^ (k & 3)) + 8 * (pc & 1);
+      if (col > o.n - 8) col = o.n - 8;
+      return k * o.ld + 2 * (col - row0);
+    }
+  }
+  // 32 bits hold every lane's distance (16 rows) below this row stride;
+  // wider operands take 64-bit addresses at every step
+  __device__ static bool wide(const Opnd& o) { return o.ld >= (int64_t)1 << 27; }
+  __device__ void init(const Opnd& o, int64_t row0, int64_t r_begin, int w, int lane) {
+    inc = MODE == KC ? KB : MODE == KF4 ? KB / 2 : Geo::KR * o.ld;
+#pragma unroll
+    for (int q = 0; q < NB; ++q)
+      b[q] = MODE == KM ? o.p + (r_begin + 8 * w) * o.ld + 2 * row0
+                        : o.p + first_row(o, row0, q, w) * o.ld + (MODE == KF4 ? r_begin / 2 : r_begin * EB);
+#pragma unroll
+    for (int q = 0; q < NV; ++q) vo[q] = (uint32_t)lane_off(o, row0, q, w, lane);
+  }
+  // reduction element (within the step) of this lane's chunk, and what takes
+  // its address back to reduction element 0 of the step
+  __device__ static int chunk4(int lane) { return (lane & 3) ^ ((lane >> 4) & 3); }
+  __device__ static int rk(int w, int lane) {
+    return MODE == KC ? 16 * chunk(w, lane) / EB : MODE == KF4 ? 32 * chunk4(lane) : 8 * w + (lane >> 3);
+  }
+  __device__ static int64_t back(int rk, int64_t ld) { return MODE == KC ? rk * EB : MODE == KF4 ? rk / 2 : rk * ld; }
+  __device__ const uint8_t* base(int q, int s) const { return b[q < NB ? q : 0] + (int64_t)s * inc; }
+  __device__ uint32_t off(int q) const { return vo[q < NV ? q : 0]; }
 };
 
 // Tile order within one problem: reduction split bz outermost; within a
@@ -251,10 +288,7 @@ struct Plan {
 // order would span 1-2 rows and 16-32 columns: they share more of their
 // operand panels in the XCD's L2 (12 panels per step instead of 18; hidden
 // 4096 block: forward -2 %, backward + SR -1.5 %).
-#ifndef GEMM_GROUP_ROWS
-#define GEMM_GROUP_ROWS 4
-#endif
-constexpr int kGroupRows = GEMM_GROUP_ROWS;
+constexpr int kGroupRows = 4;
 __host__ __device__ __forceinline__ void tile_coords(int local, int nbx, int nby, int& bx, int& by,
                                                      int& bz) {
   const int per_z = nbx * nby;
@@ -288,41 +322,36 @@ using lds_f32 = __attribute__((address_space(3))) float;
 using lds_u32 = __attribute__((address_space(3))) uint32_t;
 using lds_i32 = __attribute__((address_space(3))) int;
 
-// Stage geometry of one instantiation: bytes per stage and stages in flight.
-template <int ELEM, int MB, int KB>
+// Stage geometry of one instantiation: bytes per stage and stages (two, or
+// three with packed codes).
+template <int MB>
 struct StageGeo {
-  static constexpr int EB = ELEM == EBF16 ? 2 : 1;
-  static constexpr int SLOTB = slot_bytes<MB, KB, EB>();
-  // as many stages as fit next to the row scales (at most 4)
-  static constexpr int NS = 4 * SLOTB + TILE * 4 <= 160 * 1024 ? 4 : 3 * SLOTB + TILE * 4 <= 160 * 1024 ? 3 : 2;
+  static constexpr int SLOTB = slot_bytes<MB>();
+  static constexpr int NS = MB == KCP ? 3 : 2;
   static constexpr int kBytes = NS * SLOTB;
 };
+static_assert(StageGeo<KCP>::kBytes + TILE * 4 <= 160 * 1024, "stages fit in LDS");
 
 // The persistent grouped GEMM over the tiles of `grp`, with its LDS passed
-// in (stages, 256 row factors, a 16-entry code table, the next-tile slot),
-// so that two groups can run one after the other in one launch.
-template <int ELEM, int MA, int MB, int KB, class Epi>
+// in (stages, 256 row factors, the next-tile slot), so that two groups can
+// run one after the other in one launch.
+template <int ELEM, int MA, int MB, class Epi>
 __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem, lds_f32* row_scale,
-                                             lds_u32* code_lut, lds_i32* next_tile_p) {
-  using G = Geo<KB>;
-  static_assert(MB != KCP || KB == 128, "packed codes use 128-byte steps");
+                                             lds_i32* next_tile_p) {
+  using G = Geo;
   constexpr int EB = ELEM == EBF16 ? 2 : 1;
   constexpr int BK = KB / EB;               // reduction elements per step
   constexpr int OPB = G::OPB;
   constexpr int NL = G::NL;
-  constexpr int SLOTB = StageGeo<ELEM, MB, KB>::SLOTB;
-  constexpr int PKB = pkb<KB, EB>();
-  constexpr int NLB = Plan<MB, EB, KB>::NL;  // DMA chunks per thread for B
-  constexpr int NS = StageGeo<ELEM, MB, KB>::NS;
+  constexpr int SLOTB = StageGeo<MB>::SLOTB;
+  constexpr int NS = StageGeo<MB>::NS;
   static_assert(NW * 32 * 128 <= SLOTB, "epilogue staging (32 rows of 128 bytes per wave) fits in one stage");
-  constexpr int LPS = NL + NLB;            // DMA instructions per thread per stage (at most)
-  // (measured faster for the int8 forward, dX and dW; the e4m3 forward keeps
-  // the burst after the barrier)
-  constexpr bool kSplitCopies = ELEM != EF8 && ELEM != EF4B;
-  static_assert(ELEM != EF4B || MB == KCP || MB == KF4, "FP4 B comes from ternary codes");
-  static_assert(MB != KF4 || (ELEM == EF4B && KB == 128), "KF4 holds FP4 B of 128-element steps");
-  // bf16 operand from packed codes: two codes (a nibble) -> two bf16 by table
-  constexpr bool kLutB = MB == KCP && ELEM == EBF16;
+  // two loops: packed codes expanded in registers (ternary codes without a
+  // workspace for their expansion), and the two-phase loop for the rest
+  constexpr bool kPP = MB != KCP;
+  constexpr int CB = MB == KF4 ? 1 : 2;     // copies per wave of a half-tile of B
+  static_assert(kPP || (MA == KC && (ELEM == EI8 || ELEM == EF4B)), "packed codes meet 8-bit activations");
+  static_assert(MB == KF4 || MB == KCP || ELEM != EF4B, "FP4 B comes from ternary codes");
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -330,17 +359,6 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
   const int wi = wave / WGC, wj = wave % WGC;
   const int h = lane >> 5;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-  // packed B rows of 16 bytes need only the first CH threads' copies
-  constexpr int kChB = Plan<MB, EB, KB>::CH;
-  const bool b_copies = MB != KCP || kChB >= NTD || wave_u * 64 < kChB;
-  const int lps = NL + (b_copies ? NLB : 0);   // this wave's copies per stage
-  if constexpr (kLutB) {
-    if (tid < 16) {   // entry n: codes (n & 3, n >> 2) -> bf16 (code - 1), low half first
-      const uint32_t lo = (uint32_t)((0x00003F800000BF80ull >> (16u * (tid & 3))) & 0xFFFFu);
-      const uint32_t hi = (uint32_t)((0x00003F800000BF80ull >> (16u * (tid >> 2))) & 0xFFFFu);
-      code_lut[tid] = lo | (hi << 16);
-    }
-  }
   const int xcd = blockIdx.x & 7;
 
   // ---- state of the tile being computed
@@ -348,10 +366,10 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
     int g;
     int64_t i0, j0, rlen;
     int bz, nsteps;
-    bool tail;
+    bool tail, wide;
   };
-  Plan<MA, EB, KB> pa;
-  Plan<MB, EB, KB> pb;
+  std::conditional_t<kPP, PPlan<MA, EB, false>, Plan<KC, EB>> pa;
+  std::conditional_t<kPP, PPlan<kPP ? MB : KC, EB, true>, Plan<KCP, EB>> pb;
   TileState cur;
   float my_scale = 0.0f;
 
@@ -369,9 +387,16 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
     T.rlen = r_end > r_begin ? r_end - r_begin : 0;
     T.nsteps = (int)((T.rlen + BK - 1) / BK);
     T.tail = (T.rlen % BK) != 0;
+    T.wide = false;
     const int tid_s = opaque(tid);
-    pa.init(P.A, T.i0, r_begin, tid_s);
-    pb.init(P.B, T.j0, r_begin, tid_s);
+    if constexpr (kPP) {
+      T.wide = pa.wide(P.A) || pb.wide(P.B);
+      pa.init(P.A, T.i0, r_begin, wave_u, tid_s & 63);
+      pb.init(P.B, T.j0, r_begin, wave_u, tid_s & 63);
+    } else {
+      pa.init(P.A, T.i0, r_begin, tid_s);
+      pb.init(P.B, T.j0, r_begin, tid_s);
+    }
     if constexpr (Epi::kRowScale) {
       if (tid < TILE) {
         int64_t i = T.i0 + tid;
@@ -381,52 +406,89 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
     }
   };
 
-  // DMA of step s of the current plans into stage `slot`.
+  // (packed codes) DMA of step s of the current plans into stage `slot`
   auto issue = [&](int s, int slot, const TileState& T) {
-    lds_u8* la = smem + slot * SLOTB + wave_u * 1024;
-    lds_u8* lb = la + OPB;
-    if (!(T.tail && s == T.nsteps - 1)) {
-#pragma unroll
-      for (int q = 0; q < NL; ++q) dma16(pa.g[q] + (int64_t)s * pa.inc, la + q * (NTD * 16));
-      if (b_copies)
-#pragma unroll
-        for (int q = 0; q < NLB; ++q) dma16(pb.g[q] + (int64_t)s * pb.inc, lb + q * (NTD * 16));
-    } else {
+    if constexpr (!kPP) {
+      constexpr int NL = decltype(pa)::NL, NLB = decltype(pb)::NL;
+      lds_u8* la = smem + slot * SLOTB + wave_u * 1024;
+      lds_u8* lb = la + OPB;
+      const bool t = T.tail && s == T.nsteps - 1;
       const int64_t rbase = (int64_t)s * BK;
-      const Prob<Epi>& P = grp.p[T.g];
 #pragma unroll
-      for (int q = 0; q < NL; ++q) {
-        const bool o = rbase + pa.rk_of(q) >= T.rlen;
-        dma16(o ? pa.g[q] - pa.back_of(q, P.A.ld) : pa.g[q] + (int64_t)s * pa.inc, la + q * (NTD * 16));
-      }
-      if (b_copies)
+      for (int q = 0; q < NL; ++q)
+        dma16(t && rbase + pa.rk >= T.rlen ? pa.g[q] - pa.back : pa.g[q] + (int64_t)s * pa.inc, la + q * (NTD * 16));
 #pragma unroll
-        for (int q = 0; q < NLB; ++q) {
-          const bool o = rbase + pb.rk_of(q) >= T.rlen;
-          dma16(o ? pb.g[q] - pb.back_of(q, P.B.ld) : pb.g[q] + (int64_t)s * pb.inc, lb + q * (NTD * 16));
-        }
+      for (int q = 0; q < NLB; ++q)
+        dma16(t && rbase + pb.rk >= T.rlen ? pb.g[q] - pb.back : pb.g[q] + (int64_t)s * pb.inc, lb + q * (NTD * 16));
     }
   };
-  // zero the chunks this thread loaded past the end of the reduction (its
-  // own DMA for that stage has completed)
-  // (packed B codes past the end need no zeroing: they meet zeroed A)
-  auto zero_tail = [&](int s, int slot, const TileState& T) {
-    const int dtid = tid;
-    lds_u8* la = smem + slot * SLOTB;
-    lds_u8* lb = la + OPB;
+  // Half-tiles of a step (kPP): 0: A rows whose bit 6 is 0, 1: B columns of
+  // the waves' first column block, 2: of their second, 3: A rows whose bit 6
+  // is 1.  Two copies per wave each: chunk index and place of copy u.
+  auto half_q = [&](int w, int u) { return w == 0 || w == 3 ? (w == 3) + 2 * u : CB * (w == 2) + u; };
+  auto half_dst = [&](int w, int u, int slot) {
+    lds_u8* const st = smem + slot * SLOTB;
+    if (w == 0 || w == 3) return st + half_q(w, u) * (NTD * 16) + wave_u * 1024;
+    if (MB == KM) return st + OPB + half_q(w, u) * (NTD * 16) + wave_u * 1024;
+    if (MB == KF4) return st + OPB + (wave_u >> 1) * 4096 + (w == 2 ? 2048 : 0) + (wave_u & 1) * 1024;
+    return st + OPB + u * 16384 + (wave_u >> 2) * 8192 + (w == 2 ? 4096 : 0) + (wave_u & 3) * 1024;
+  };
+  // Copy u of half-tile w of step s.  maybe_tail: the step may end past the
+  // reduction; lanes past it then load the step's first chunk of their row
+  // (or its first reduction row), which is inside.
+  auto issue_copy = [&](int w, int u, int s, int slot, const TileState& T, auto maybe_tail) {
+    if constexpr (kPP) {
+    const bool is_a = w == 0 || w == 3;
+    const int q = half_q(w, u);
+    const uint8_t* const b = is_a ? pa.base(q, s) : pb.base(q, s);
+    if constexpr (decltype(maybe_tail)::value) {
+      if (T.wide || (T.tail && s == T.nsteps - 1)) {
+        const int lane_s = opaque(lane);
+        const Opnd& o = is_a ? grp.p[T.g].A : grp.p[T.g].B;
+        const int rk = is_a ? pa.rk(wave_u, lane_s) : pb.rk(wave_u, lane_s);
+        const int64_t back = is_a ? pa.back(rk, o.ld) : pb.back(rk, o.ld);
+        const int64_t off = is_a ? pa.lane_off(o, T.i0, q, wave_u, lane_s) : pb.lane_off(o, T.j0, q, wave_u, lane_s);
+        dma16(b + off - ((int64_t)s * BK + rk >= T.rlen ? back : 0), half_dst(w, u, slot));
+        return;
+      }
+    }
+    dma16s(b, is_a ? pa.off(q) : pb.off(q), half_dst(w, u, slot));
+    }
+  };
+  auto issue_half = [&](int w, int s, int slot, const TileState& T) {
+    issue_copy(w, 0, s, slot, T, std::true_type{});
+    if (w == 0 || w == 3 || CB == 2) issue_copy(w, 1, s, slot, T, std::true_type{});
+  };
+  auto zero_half = [&](int w, int s, int slot, const TileState& T) {
+    // (FP4 values past the end need no zeroing: they meet zeroed A, and FP4
+    // has no NaN and no infinity)
+    if constexpr (kPP) {
+    if (MB == KF4 && (w == 1 || w == 2)) return;
     const int64_t rbase = (int64_t)s * BK;
     const i32x4 z = {0, 0, 0, 0};
 #pragma unroll
-    for (int q = 0; q < NL; ++q)
-      if (rbase + pa.rk_of(q) >= T.rlen) *(__attribute__((address_space(3))) i32x4*)(la + (q * NTD + dtid) * 16) = z;
-    // (packed codes and FP4 values past the end need no zeroing: they meet
-    // zeroed A, and neither holds a NaN or an infinity)
-    if constexpr (MB != KCP && MB != KF4)
+    for (int u = 0; u < 2; ++u) {
+      const int rk = w == 0 || w == 3 ? pa.rk(wave_u, lane) : pb.rk(wave_u, lane);
+      if (rbase + rk >= T.rlen) *(__attribute__((address_space(3))) i32x4*)(half_dst(w, u, slot) + lane * 16) = z;
+    }
+    }
+  };
+  // (packed codes) zero the chunks of A this thread loaded past the end of the
+  // reduction (its own DMA for that stage has completed); packed codes past
+  // the end need no zeroing: they meet zeroed A
+  auto zero_tail = [&](int s, int slot, const TileState& T) {
+    if constexpr (!kPP) {
+      lds_u8* la = smem + slot * SLOTB;
+      const i32x4 z = {0, 0, 0, 0};
 #pragma unroll
-      for (int q = 0; q < NL; ++q)
-        if (rbase + pb.rk_of(q) >= T.rlen) *(__attribute__((address_space(3))) i32x4*)(lb + (q * NTD + dtid) * 16) = z;
+      for (int q = 0; q < decltype(pa)::NL; ++q)
+        if ((int64_t)s * BK + pa.rk >= T.rlen) *(__attribute__((address_space(3))) i32x4*)(la + (q * NTD + tid) * 16) = z;
+    }
   };
 
+  // first column of this wave's column block t: the two blocks are adjacent,
+  // or (K-major B, whose halves are 128 columns) 128 apart
+  auto col_of = [&](int t) { return MB == KM ? 128 * t + 32 * wj : wj * 32 * WJ + t * 32; };
   using AccV = typename AccT<ELEM == EI8 ? Mfma::I8 : Mfma::BF16>::type;
   AccV acc[WI][WJ];
 
@@ -434,110 +496,46 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
   const int frow = lane & 31;
   const int t4 = (lane >> 2) & 3, u4 = lane & 3, ch = (lane >> 4) & 1;
 
-  // Fragments of one reduction sub-step kk (0..3; 32 bytes of reduction per
-  // tile row): K-contiguous ones by ds_read_b128, K-major ones by two
-  // transposing reads (inline asm, waited for by frag_wait).
+  // (packed codes) Fragments of one reduction sub-step kk (0..3; 32 bytes of
+  // reduction per tile row).  pq: this lane's 16-byte half of each B row (64
+  // codes, read once per step; sub-step kk in word kk).  Lane half h then
+  // takes reduction elements 64 h .. 64 h + 63 of the step, sub-step kk the 16
+  // from 64 h + 16 kk, and its A chunks follow the same order: chunk 4 h + kk
+  // instead of 2 kk + h.  (One 16-byte read per row half is free of bank
+  // conflicts; four 4-byte reads of words 2 kk + h, all lanes at one word
+  // offset in 32-byte rows, conflicted 4-way and cost the e4m3 forward 9 %.)
   struct Frags {
-    i32x4 fa[WI], fb[WJ];
-    u32x2 ka[WI][2], kb[WJ][2];
+    i32x4 fa[WI];
     uint32_t pb[WJ];          // packed codes (16 per lane), expanded at use
   };
-  // pk: bf16 steps from packed codes, this lane's 64 bits of each B row
-  // (sub-step kk in bits 16 kk .. 16 kk + 15, read once per step).
-  // pq: 8-bit steps from packed codes, this lane's 16-byte half of each B
-  // row (64 codes, read once per step; sub-step kk in word kk).  Lane half h
-  // then takes reduction elements 64 h .. 64 h + 63 of the step, sub-step kk
-  // the 16 from 64 h + 16 kk, and its A chunks follow the same order: chunk
-  // 4 h + kk instead of 2 kk + h.  (One 16-byte read per row half is free of
-  // bank conflicts; four 4-byte reads of words 2 kk + h, all lanes at one
-  // word offset in 32-byte rows, conflicted 4-way and cost the e4m3 forward
-  // 9 %.)
-  constexpr bool kPq = MB == KCP && !kLutB;
-  auto read_frags = [&](const lds_u8* la, const lds_u8* lb, int kk, Frags& F, const u32x2* pk,
-                        const i32x4* pq) {
+  auto read_frags = [&](const lds_u8* la, int kk, Frags& F, const i32x4* pq) {
 #pragma unroll
     for (int t = 0; t < WI; ++t) {
-      if constexpr (MA == KC) {
-        const int row = wi * 32 * WI + t * 32 + frow;
-        const int c = (kPq ? 4 * h + kk : 2 * kk + h) ^ G::swz(row);
-        F.fa[t] = *(const __attribute__((address_space(3))) i32x4*)(la + row * KB + 16 * c);
-      } else {
-        const int col = wi * 32 * WI + t * 32 + 16 * ch + 4 * u4;
-        const int seg = ((col & 63) >> 4) ^ t4;
-        const int a0 = (col >> 6) * (G::KR * 128) + (16 * kk + 8 * h + t4) * 128 + 32 * seg + 8 * u4;
-        F.ka[t][0] = tr_read(la, a0);
-        F.ka[t][1] = tr_read(la, a0 + 512);
-      }
+      const int row = wi * 32 * WI + t * 32 + frow;
+      F.fa[t] = *(const __attribute__((address_space(3))) i32x4*)(la + row * KB + 16 * ((4 * h + kk) ^ G::swz(row)));
     }
 #pragma unroll
-    for (int t = 0; t < WJ; ++t) {
-      if constexpr (kLutB) {
-        const uint32_t x16 = (pk[t][kk >> 1] >> (16 * (kk & 1))) & 0xFFFFu;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) F.fb[t][i] = (int)code_lut[(x16 >> (4 * i)) & 0xFu];
-      } else if constexpr (MB == KCP) {
-        F.pb[t] = (uint32_t)pq[t][kk];
-      } else if constexpr (MB == KF4) {
-        // the FP4 operand of sub-step pair m = kk / 2 (read with its even
-        // sub-step): lane half h takes the row's 32 values from 64 m + 32 h,
-        // which are the elements its e4m3 partner lanes pair them with
-        if ((kk & 1) == 0) {
-          const int row = wj * 32 * WJ + t * 32 + frow;
-          const int c = (kk + h) ^ ((row >> 2) & 3);
-          F.fb[t] = *(const __attribute__((address_space(3))) i32x4*)(lb + row * (KB / 2) + 16 * c);
-        }
-      } else if constexpr (MB == KC) {
-        const int row = wj * 32 * WJ + t * 32 + frow;
-        const int c = (2 * kk + h) ^ G::swz(row);
-        F.fb[t] = *(const __attribute__((address_space(3))) i32x4*)(lb + row * KB + 16 * c);
-      } else {
-        const int col = wj * 32 * WJ + t * 32 + 16 * ch + 4 * u4;
-        const int seg = ((col & 63) >> 4) ^ t4;
-        const int a0 = (col >> 6) * (G::KR * 128) + (16 * kk + 8 * h + t4) * 128 + 32 * seg + 8 * u4;
-        F.kb[t][0] = tr_read(lb, a0);
-        F.kb[t][1] = tr_read(lb, a0 + 512);
-      }
-    }
+    for (int t = 0; t < WJ; ++t) F.pb[t] = (uint32_t)pq[t][kk];
   };
-  auto opa = [&](const Frags& F, int t) { return MA == KC ? F.fa[t] : join(F.ka[t][0], F.ka[t][1]); };
-  auto opb = [&](const Frags& F, int t) {
-    if constexpr (kLutB) return F.fb[t];
-    else if constexpr (MB == KCP) return expand16(F.pb[t], ELEM == EF8 ? 0x003800B8u : 0x000100FFu);
-    else return MB == KC || MB == KF4 ? F.fb[t] : join(F.kb[t][0], F.kb[t][1]);
-  };
-  // MFMAs of one sub-step (int8 / bf16), or of two sub-steps (e4m3, whose
-  // instruction reduces 64 elements: sub-step pairs (0, 1) and (2, 3)).
+  // MFMAs of one sub-step (int8), or of two (e4m3, whose instruction reduces
+  // 64 elements: sub-step pairs (0, 1) and (2, 3)).
   auto mfma1 = [&](const Frags& F) {
+    if constexpr (!kPP && ELEM == EI8) {
 #pragma unroll
-    for (int ta = 0; ta < WI; ++ta)
+      for (int ta = 0; ta < WI; ++ta)
 #pragma unroll
-      for (int tb = 0; tb < WJ; ++tb) {
-        if constexpr (ELEM == EI8)
-          acc[ta][tb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(opb(F, tb), opa(F, ta), acc[ta][tb], 0, 0, 0);
-        else if constexpr (Epi::kTrans)   // lanes hold four consecutive rows of one column
-          acc[ta][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, opa(F, ta)),
-                                                                __builtin_bit_cast(bf16x8, opb(F, tb)),
-                                                                acc[ta][tb], 0, 0, 0);
-        else
-          acc[ta][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, opb(F, tb)),
-                                                                __builtin_bit_cast(bf16x8, opa(F, ta)),
-                                                                acc[ta][tb], 0, 0, 0);
-      }
+        for (int tb = 0; tb < WJ; ++tb)
+          acc[ta][tb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(expand16(F.pb[tb], 0x000100FFu), F.fa[ta], acc[ta][tb], 0, 0, 0);
+    }
   };
   auto mfma2 = [&](const Frags& F0, const Frags& F1) {
+    if constexpr (!kPP && ELEM == EF4B) {
 #pragma unroll
-    for (int ta = 0; ta < WI; ++ta)
+      for (int ta = 0; ta < WI; ++ta)
 #pragma unroll
-      for (int tb = 0; tb < WJ; ++tb) {
-        const i32x4 a0 = opa(F0, ta), a1 = opa(F1, ta), b0 = opb(F0, tb), b1 = opb(F1, tb);
-        const i32x8 av = {a0[0], a0[1], a0[2], a0[3], a1[0], a1[1], a1[2], a1[3]};
-        const i32x8 bv = {b0[0], b0[1], b0[2], b0[3], b1[0], b1[1], b1[2], b1[3]};
-        if constexpr (ELEM == EF4B && MB == KF4) {
-          // FP4 B from the workspace, already in the instruction's order
-          const i32x4 f = F0.fb[tb];
-          const i32x8 bv4 = {f[0], f[1], f[2], f[3], 0, 0, 0, 0};
-          acc[ta][tb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(bv4, av, acc[ta][tb], 4, 0, 0, 127, 0, 127);
-        } else if constexpr (ELEM == EF4B) {
+        for (int tb = 0; tb < WJ; ++tb) {
+          const i32x4 a0 = F0.fa[ta], a1 = F1.fa[ta];
+          const i32x8 av = {a0[0], a0[1], a0[2], a0[3], a1[0], a1[1], a1[2], a1[3]};
           // B as FP4 (format 4: 32 values in the first four registers), A
           // e4m3 (format 0), unit E8M0 scales (127 = 2^0).  With FP4 the
           // first operand's lane half h holds reduction elements 16 h ..
@@ -552,11 +550,8 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
           const u32x2 f0 = expand16_fp4(sw[0]), f1 = expand16_fp4(sw[1]);
           const i32x8 bv4 = {(int)f0[0], (int)f0[1], (int)f1[0], (int)f1[1], 0, 0, 0, 0};
           acc[ta][tb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(bv4, av, acc[ta][tb], 4, 0, 0, 127, 0, 127);
-        } else {
-          // both operands e4m3 (format 0), unit E8M0 scales (127 = 2^0)
-          acc[ta][tb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(bv, av, acc[ta][tb], 0, 0, 0, 127, 0, 127);
         }
-      }
+    }
   };
   auto stage_ptr = [&](int slot) { return smem + slot * SLOTB; };
 
@@ -572,70 +567,59 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
   // Stage of step s of the current tile: (slot0 + s) mod NS.  Before a tile
   // starts, its steps 0 .. NS-2 are in flight.
   int slot0 = 0;
-  for (int s = 0; s < NS - 1 && s < cur.nsteps; ++s) issue(s, s, cur);
+  auto prefetch = [&](int slot) {
+    if constexpr (kPP) {
+      if (cur.nsteps > 0) {
+#pragma unroll
+        for (int w = 0; w < 4; ++w) issue_half(w, 0, slot, cur);
+      }
+    } else {
+      for (int s = 0; s < NS - 1 && s < cur.nsteps; ++s) issue(s, (slot + s) % NS, cur);
+    }
+  };
+  prefetch(0);
 
-  // One step from stage `slot`: sub-step kk+1's fragments load while kk's
-  // MFMAs run (e4m3: sub-steps are consumed in pairs).
-  auto compute = [&](int slot, auto&& mid) {
+  // (packed codes) One step from stage `slot`: sub-step kk+1's fragments load
+  // while kk's MFMAs run (e4m3: sub-steps are consumed in pairs).
+  auto compute = [&](int slot) {
     const lds_u8* la = stage_ptr(slot);
     const lds_u8* lb = la + OPB;
-    // (scheduling barriers keep each group of reads ahead of the MFMAs that
-    // precede their use; left alone, the compiler sinks every read next to
-    // its first use and exposes the LDS latency)
-    u32x2 pk[WJ];
-    if constexpr (kLutB) {
-#pragma unroll
-      for (int t = 0; t < WJ; ++t) {
-        // the packing swaps the two 8-byte halves of rows with bit 4 set
-        const int row = wj * 32 * WJ + t * 32 + frow;
-        pk[t] = *(const __attribute__((address_space(3))) u32x2*)(lb + row * 16 + 8 * (h ^ ((row >> 4) & 1)));
-      }
-    }
     // (the DMA stores logical 16-byte half c of row r at half c ^ ((r >> 3) & 1))
     i32x4 pq[WJ];
-    if constexpr (kPq) {
 #pragma unroll
-      for (int t = 0; t < WJ; ++t) {
-        const int row = wj * 32 * WJ + t * 32 + frow;
-        pq[t] = *(const __attribute__((address_space(3))) i32x4*)(lb + row * PKB + 16 * (h ^ ((row >> 3) & 1)));
-      }
+    for (int t = 0; t < WJ; ++t) {
+      const int row = wj * 32 * WJ + t * 32 + frow;
+      pq[t] = *(const __attribute__((address_space(3))) i32x4*)(lb + row * PKB + 16 * (h ^ ((row >> 3) & 1)));
     }
     Frags F0, F1;
-    if constexpr (ELEM != EF8 && ELEM != EF4B) {
-      read_frags(la, lb, 0, F0, pk, pq);
-      read_frags(la, lb, 1, F1, pk, pq);
+    if constexpr (ELEM == EI8) {
+      // (scheduling barriers keep each group of reads ahead of the MFMAs that
+      // precede their use; left alone, the compiler sinks every read next to
+      // its first use and exposes the LDS latency)
+      read_frags(la, 0, F0, pq);
+      read_frags(la, 1, F1, pq);
       __builtin_amdgcn_sched_barrier(0);
       mfma1(F0);
       __builtin_amdgcn_sched_barrier(0);
-      mid();
+      read_frags(la, 2, F0, pq);
       __builtin_amdgcn_sched_barrier(0);
-      if constexpr (G::NKK == 4) {
-        read_frags(la, lb, 2, F0, pk, pq);
-        __builtin_amdgcn_sched_barrier(0);
-        mfma1(F1);
-        __builtin_amdgcn_sched_barrier(0);
-        read_frags(la, lb, 3, F1, pk, pq);
-        __builtin_amdgcn_sched_barrier(0);
-        mfma1(F0);
-        __builtin_amdgcn_sched_barrier(0);
-      }
+      mfma1(F1);
+      __builtin_amdgcn_sched_barrier(0);
+      read_frags(la, 3, F1, pq);
+      __builtin_amdgcn_sched_barrier(0);
+      mfma1(F0);
+      __builtin_amdgcn_sched_barrier(0);
       mfma1(F1);
     } else {
       // (e4m3 keeps the compiler's own order: a pair of sub-steps per
       // instruction leaves no registers for a further pair in flight)
-      read_frags(la, lb, 0, F0, pk, pq);
-      read_frags(la, lb, 1, F1, pk, pq);
-      if constexpr (G::NKK == 4) {
-        Frags F2, F3;
-        read_frags(la, lb, 2, F2, pk, pq);
-        mfma2(F0, F1);
-        mid();
-        read_frags(la, lb, 3, F3, pk, pq);
-        mfma2(F2, F3);
-      } else {
-        mfma2(F0, F1);
-        mid();
-      }
+      Frags F2, F3;
+      read_frags(la, 0, F0, pq);
+      read_frags(la, 1, F1, pq);
+      read_frags(la, 2, F2, pq);
+      mfma2(F0, F1);
+      read_frags(la, 3, F3, pq);
+      mfma2(F2, F3);
     }
   };
 
@@ -648,7 +632,6 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
   // at issue beyond that), so "at most 63 newer" is a correct, if
   // conservative, wait when more were issued
   constexpr int kVmMax = 63;
-  static_assert(NS * LPS < kVmMax, "vmcnt range");
   uint8_t* const dummy = reinterpret_cast<uint8_t*>(grp.sched) + 128;
   bool first_tile = true;
   int stores_prev = 0;                 // stores per thread of the previous epilogue
@@ -662,8 +645,203 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
       sr_cnt[2 * wave_u + 1] = 0;
     }
   }
+  int fetched = 0;                     // thread 0: index of the next tile
+  // The main loop of kPP: a step's 128 x 64 outputs per wave as four quarters
+  // (64 rows x 32 columns: A half x B half), each a phase of
+  //   memory: fragments of the half-tile the quarter needs new, copies of one
+  //           half-tile of a later step, the wait for a half-tile needed next;
+  //   compute: 8 matrix instructions.
+  // The second four waves (each shares its SIMD with one of the first four)
+  // run one half-phase behind, so on every SIMD one wave's memory part always
+  // runs beside the other's matrix instructions, and the copies are spread
+  // over the step, five half-tiles (80 KB) in flight.
+  auto pp_loop = [&]() {
+    const int n = cur.nsteps;
+    if (n == 0) return;
+    const bool g2 = wave_u >= NW / 2;
+    {
+      // step 0's copies were issued before the previous epilogue's stores
+      if (first_tile) wait_vm<0>();
+      else if (Epi::kSR) wait_vm<kStoresSR>();
+      else if (stores_prev == kStoresBf16) wait_vm<kStoresBf16>();
+      else wait_vm<kStoresF32 < kVmMax ? kStoresF32 : kVmMax>();
+      first_tile = false;
+    }
+    if (cur.tail && n == 1) {
+#pragma unroll
+      for (int w = 0; w < 4; ++w) zero_half(w, 0, slot0, cur);
+    }
+    block_barrier();                   // step 0 complete; the other stage is free
+    if (n > 1) {
+#pragma unroll
+      for (int w = 0; w < 3; ++w) issue_half(w, 1, slot0 ^ 1, cur);
+    }
+    if (tid == 0) fetched = atomicAdd(next_ctr, 1);
+    if (g2) block_barrier();
+    // (e4m3: a pair of sub-steps is one operand of eight registers)
+    constexpr bool kF8 = ELEM == EF8 || ELEM == EF4B;
+    struct HA { i32x4 f[2][4]; u32x2 k[2][4][2]; i32x8 p[2][2]; };
+    struct HB { i32x4 f[4]; u32x2 k[4][2]; i32x8 p[2]; };
+    auto put4 = [](i32x8& d, int hi, i32x4 v) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) d[4 * hi + e] = v[e];
+    };
+    auto read_a = [&](const lds_u8* la, int hf, HA& F) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+          if constexpr (MA == KC) {
+            const int row = wi * 128 + 64 * hf + 32 * t + frow;
+            const i32x4 v = *(const __attribute__((address_space(3))) i32x4*)(la + row * KB + 16 * ((2 * kk + h) ^ G::swz(row)));
+            if constexpr (kF8) put4(F.p[t][kk >> 1], kk & 1, v);
+            else F.f[t][kk] = v;
+          } else {
+            const int col = wi * 128 + 64 * hf + 32 * t + 16 * ch + 4 * u4;
+            const int seg = ((col & 63) >> 4) ^ t4;
+            const int a0 = (col >> 6) * (G::KR * 128) + (16 * kk + 8 * h + t4) * 128 + 32 * seg + 8 * u4;
+            F.k[t][kk][0] = tr_read(la, a0);
+            F.k[t][kk][1] = tr_read(la, a0 + 512);
+          }
+        }
+    };
+    auto read_b = [&](const lds_u8* lb, int t, HB& F) {
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        if constexpr (MB == KF4) {
+          // sub-step pair kk / 2: lane half h takes the row's 32 values from
+          // 64 (kk / 2) + 32 h, which its e4m3 partner lanes pair them with
+          const int row = wj * 64 + t * 32 + frow;
+          if ((kk & 1) == 0)
+            F.f[kk >> 1] = *(const __attribute__((address_space(3))) i32x4*)(lb + row * 64 + 16 * ((kk + h) ^ ((row >> 2) & 3)));
+        } else if constexpr (MB == KC) {
+          const int row = wj * 64 + t * 32 + frow;
+          const i32x4 v = *(const __attribute__((address_space(3))) i32x4*)(lb + row * KB + 16 * ((2 * kk + h) ^ G::swz(row)));
+          if constexpr (kF8) put4(F.p[kk >> 1], kk & 1, v);
+          else F.f[kk] = v;
+        } else {
+          const int col = col_of(t) + 16 * ch + 4 * u4;
+          const int seg = ((col & 63) >> 4) ^ t4;
+          const int a0 = (col >> 6) * (G::KR * 128) + (16 * kk + 8 * h + t4) * 128 + 32 * seg + 8 * u4;
+          F.k[kk][0] = tr_read(lb, a0);
+          F.k[kk][1] = tr_read(lb, a0 + 512);
+        }
+      }
+    };
+    auto quarter = [&](const HA& A, const HB& B, int hf, int tb) {
+      __builtin_amdgcn_sched_barrier(0);
+      block_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (ELEM == EF8 || ELEM == EF4B) {
+        // unit E8M0 scales (127 = 2^0); B e4m3 (format 0) or FP4 (format 4)
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+          for (int t = 0; t < 2; ++t) {
+            const i32x8 av = A.p[t][m];
+            AccV& c = acc[2 * hf + t][tb];
+            if constexpr (ELEM == EF4B) {
+              const i32x4 f = B.f[m];
+              const i32x8 bv = {f[0], f[1], f[2], f[3], 0, 0, 0, 0};
+              c = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(bv, av, c, 4, 0, 0, 127, 0, 127);
+            } else {
+              c = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(B.p[m], av, c, 0, 0, 0, 127, 0, 127);
+            }
+          }
+      } else {
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const i32x4 a = MA == KC ? A.f[t][kk] : join(A.k[t][kk][0], A.k[t][kk][1]);
+          const i32x4 b = MB == KC ? B.f[kk] : join(B.k[kk][0], B.k[kk][1]);
+          AccV& c = acc[2 * hf + t][tb];
+          if constexpr (ELEM == EI8)
+            c = __builtin_amdgcn_mfma_i32_32x32x32_i8(b, a, c, 0, 0, 0);
+          else if constexpr (Epi::kTrans)
+            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+          else
+            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, b), __builtin_bit_cast(bf16x8, a), c, 0, 0, 0);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      block_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    // One step.  Each phase: its fragment reads first, then one half-tile's
+    // copies (issued ahead of the reads they delayed them: hidden-4096
+    // backward + SR 6.3 against 5.6 ms; one copy in the compute part held up
+    // the matrix instructions: 6.2 ms), then the wait for the half-tile that
+    // the next phase reads: all but the copies newer than it.  The first
+    // half-tile of B is read a step ahead, in the fourth phase, so that the
+    // phases read 8, 4, 8 and 4 fragments (read in the first phase: 5.14
+    // against 5.06 ms).  STEADY: steps s + 1 and s + 2 exist and are whole.
+    // (e4m3 B keeps it in the first phase: its eight-register operands would
+    // be copied from one step to the next)
+    constexpr bool kEarlyB = ELEM != EF8;
+    HB B0;
+    if constexpr (kEarlyB) read_b(stage_ptr(slot0) + OPB, 0, B0);
+    auto step = [&](int s, auto steady) {
+      constexpr bool ST = decltype(steady)::value;
+      constexpr std::bool_constant<!ST> mt{};
+      const int rem = n - 1 - s;
+      const bool f1 = ST || rem >= 1, f2 = ST || rem >= 2;
+      const bool ztail = !ST && cur.tail && n > 1;
+      const int slot = slot0 ^ (s & 1);
+      const lds_u8* la = stage_ptr(slot);
+      const lds_u8* lb = la + OPB;
+      auto copies = [&](int w, int at, int to) {
+#pragma unroll
+        for (int u = 0; u < (w == 0 || w == 3 ? 2 : CB); ++u) issue_copy(w, u, at, to, cur, mt);
+      };
+      HA A;
+      HB B1;
+      read_a(la, 0, A);
+      if constexpr (!kEarlyB) read_b(lb, 0, B0);
+      if (f1) {
+        copies(3, s + 1, slot ^ 1);
+        wait_vm<6 + 2 * CB>();
+      } else {
+        wait_vm<2>();
+        if (ztail) zero_half(2, s, slot, cur);
+      }
+      quarter(A, B0, 0, 0);
+      read_b(lb, 1, B1);
+      if (f2) {
+        copies(0, s + 2, slot);
+        wait_vm<6 + 2 * CB>();
+      } else if (f1) {
+        wait_vm<4 + 2 * CB>();
+      } else {
+        wait_vm<0>();
+        if (ztail) zero_half(3, s, slot, cur);
+      }
+      quarter(A, B1, 0, 1);
+      read_a(la, 1, A);
+      if (f2) {
+        copies(1, s + 2, slot);
+        wait_vm<4 + 2 * CB>();
+      } else if (f1) {
+        wait_vm<2 + CB>();
+        if (ztail) {
+          zero_half(0, s + 1, slot ^ 1, cur);
+          zero_half(1, s + 1, slot ^ 1, cur);
+        }
+      }
+      quarter(A, B1, 1, 1);
+      HB Bn;
+      if (kEarlyB && f1) read_b(stage_ptr(slot ^ 1) + OPB, 0, Bn);
+      if (f2) copies(2, s + 2, slot);
+      quarter(A, B0, 1, 0);
+      if (kEarlyB && f1) B0 = Bn;
+    };
+    int s = 0;
+    for (const int ns = cur.wide ? 0 : n - 2 - (cur.tail ? 1 : 0); s < ns; ++s) step(s, std::true_type{});
+    for (; s < n; ++s) step(s, std::false_type{});
+    if (!g2) block_barrier();
+  };
   for (;;) {
-    int fetched = 0;                   // thread 0: index of the next tile
+    fetched = 0;
 #pragma unroll
     for (int a = 0; a < WI; ++a)
 #pragma unroll
@@ -671,40 +849,35 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[a][b][r] = 0;
 
-    // main loop: step it computes from stage (slot0 + it) mod NS while the
-    // next NS - 1 steps load into the other stages.  The first step of a
-    // tile waits for every load and store of this thread (the previous
-    // epilogue's stores were issued after this tile's first stages).
-    for (int it = 0; it < cur.nsteps; ++it) {
-      const int slot = (slot0 + it) % NS;
-      if (it == 0) {
-        // step 0's loads were issued before the previous epilogue's stores
-        // (a fixed number per thread), which may stay in flight, as may the
-        // tile's later prefetched steps
-        const int ahead = (cur.nsteps < NS - 1 ? cur.nsteps : NS - 1) - 1;
-        int n = ahead * lps + (first_tile ? 0 : stores_prev);
-        if (n > kVmMax) n = kVmMax;
-        wait_vm_le<kVmMax>(__builtin_amdgcn_readfirstlane(n));
-        first_tile = false;
-      } else {
-        // copies of steps it + 1 .. it + NS - 2 (those issued) may stay in flight
-        const int newer = cur.nsteps - 1 - it < NS - 2 ? cur.nsteps - 1 - it : NS - 2;
-        if constexpr (NS == 2) wait_vm<0>();
-        else wait_vm_le<(NS - 2) * LPS>(__builtin_amdgcn_readfirstlane(newer * lps));
+    if constexpr (kPP) {
+      pp_loop();
+    } else {
+      // step it computes from stage (slot0 + it) mod NS while the next NS - 1
+      // steps load into the other stages.  Step 0's loads were issued before
+      // the previous epilogue's stores (a fixed number per thread), which may
+      // stay in flight, as may the tile's later prefetched steps.
+      constexpr int LPS = decltype(pa)::NL + decltype(pb)::NL;   // copies per thread per stage
+      static_assert(NS * LPS < kVmMax, "vmcnt range");
+      for (int it = 0; it < cur.nsteps; ++it) {
+        const int slot = (slot0 + it) % NS;
+        if (it == 0) {
+          const int ahead = (cur.nsteps < NS - 1 ? cur.nsteps : NS - 1) - 1;
+          int n = ahead * LPS + (first_tile ? 0 : stores_prev);
+          if (n > kVmMax) n = kVmMax;
+          wait_vm_le<kVmMax>(__builtin_amdgcn_readfirstlane(n));
+          first_tile = false;
+        } else {
+          // copies of steps it + 1 .. it + NS - 2 (those issued) may stay in flight
+          const int newer = cur.nsteps - 1 - it < NS - 2 ? cur.nsteps - 1 - it : NS - 2;
+          wait_vm_le<(NS - 2) * LPS>(__builtin_amdgcn_readfirstlane(newer * LPS));
+        }
+        if (cur.tail && it == cur.nsteps - 1) zero_tail(it, slot, cur);
+        block_barrier();                 // stage `slot` complete; step it - 1's stage is free
+        if (it + NS - 1 < cur.nsteps) issue(it + NS - 1, (slot + NS - 1) % NS, cur);
+        // fetch the next tile early; its value is needed only at the epilogue
+        if (it == 0 && tid == 0) fetched = atomicAdd(next_ctr, 1);
+        compute(slot);
       }
-      if (cur.tail && it == cur.nsteps - 1) zero_tail(it, slot, cur);
-      block_barrier();                 // stage `slot` complete; step it - 1's stage is free
-      // The two waves of a SIMD take turns: the first half of the waves
-      // issues its copies right after the barrier, the other half after its
-      // first group of MFMAs, so each SIMD has one wave issuing MFMAs while
-      // the other waits for its copies to be taken.
-      const bool copy_now = !kSplitCopies || wave_u < NW / 2;
-      if (copy_now && it + NS - 1 < cur.nsteps) issue(it + NS - 1, (slot + NS - 1) % NS, cur);
-      // fetch the next tile early; its value is needed only at the epilogue
-      if (it == 0 && tid == 0) fetched = atomicAdd(next_ctr, 1);
-      compute(slot, [&]() {
-        if (!copy_now && it + NS - 1 < cur.nsteps) issue(it + NS - 1, (slot + NS - 1) % NS, cur);
-      });
     }
 
     // epilogue parameters of this tile, then the next tile's first stage
@@ -728,17 +901,11 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
     [[maybe_unused]] uint32_t srt[Epi::kSR ? WI : 1][Epi::kSR ? WJ : 1];
     [[maybe_unused]] uint32_t sr8[Epi::kSR && !Epi::kTern ? WI : 1][Epi::kSR && !Epi::kTern ? WJ : 1][2][2];
     auto sr_pos = [&](int ta, int tb, int u, int64_t& n, int64_t& k) {
-      if constexpr (Epi::kTrans) {
-        // block (ta, tb) of dW^T holds dW rows j0 + .. + 32 tb (d_out) and
-        // columns i0 + .. + 32 ta (d_in), laid out as a block of dW
-        n = j0 + wj * 32 * WJ + tb * 32 + sr_r + 16 * u;
-        k = i0 + wi * 32 * WI + ta * 32 + 8 * sr_c;
-        return n < J && k < I;
-      } else {
-        n = i0 + wi * 32 * WI + ta * 32 + sr_r + 16 * u;
-        k = j0 + wj * 32 * WJ + tb * 32 + 8 * sr_c;
-        return n < I && k < J;
-      }
+      // block (ta, tb) of dW^T holds dW rows j0 + col_of(tb) + .. (d_out) and
+      // columns i0 + .. + 32 ta (d_in), laid out as a block of dW
+      n = j0 + col_of(tb) + sr_r + 16 * u;
+      k = i0 + wi * 32 * WI + ta * 32 + 8 * sr_c;
+      return n < J && k < I;
     };
     if constexpr (Epi::kSR) {
 #pragma unroll
@@ -780,7 +947,7 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
     if (more) {
       const int slotn = (last + 1) % NS;      // the next tile's stages avoid `last`
       setup(gn, localn, cur);
-      for (int s = 0; s < NS - 1 && s < cur.nsteps; ++s) issue(s, (slotn + s) % NS, cur);
+      prefetch(slotn);
       slot0 = slotn;
     }
 
@@ -974,31 +1141,26 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
   }
 }
 
-template <int ELEM, int MA, int MB, int KB, class Epi>
+template <int ELEM, int MA, int MB, class Epi>
 __global__ __launch_bounds__(NTH) void gemm_v3_kernel(const Group<Epi> grp) {
-  __shared__ __attribute__((aligned(1024))) uint8_t stages[StageGeo<ELEM, MB, KB>::kBytes];
+  __shared__ __attribute__((aligned(1024))) uint8_t stages[StageGeo<MB>::kBytes];
   __shared__ float row_scale[TILE];
-  __shared__ uint32_t code_lut[16];
   __shared__ int next_tile;
-  gemm_v3_body<ELEM, MA, MB, KB, Epi>(grp, (lds_u8*)stages, (lds_f32*)row_scale, (lds_u32*)code_lut,
-                                       (lds_i32*)&next_tile);
+  gemm_v3_body<ELEM, MA, MB, Epi>(grp, (lds_u8*)stages, (lds_f32*)row_scale, (lds_i32*)&next_tile);
 }
 
-// Two groups in one launch: every block takes tiles of the first group until
-// its lists are empty, then tiles of the second, so blocks left without a
-// tile of the first start on the second at once.
-template <int E1, int MA1, int MB1, int KB1, class Epi1, int E2, int MA2, int MB2, int KB2, class Epi2>
+// Two groups of bf16 products in one launch: every block takes tiles of the
+// first group until its lists are empty, then tiles of the second, so blocks
+// left without a tile of the first start on the second at once.
+template <int MA1, int MB1, class Epi1, int MA2, int MB2, class Epi2>
 __global__ __launch_bounds__(NTH) void gemm_v3_dual_kernel(const Group<Epi1> g1, const Group<Epi2> g2) {
-  constexpr int B1 = StageGeo<E1, MB1, KB1>::kBytes, B2 = StageGeo<E2, MB2, KB2>::kBytes;
-  __shared__ __attribute__((aligned(1024))) uint8_t stages[B1 > B2 ? B1 : B2];
+  static_assert(StageGeo<MB1>::kBytes == StageGeo<MB2>::kBytes, "one stage area");
+  __shared__ __attribute__((aligned(1024))) uint8_t stages[StageGeo<MB1>::kBytes];
   __shared__ float row_scale[TILE];
-  __shared__ uint32_t code_lut[16];
   __shared__ int next_tile;
-  gemm_v3_body<E1, MA1, MB1, KB1, Epi1>(g1, (lds_u8*)stages, (lds_f32*)row_scale, (lds_u32*)code_lut,
-                                         (lds_i32*)&next_tile);
+  gemm_v3_body<EBF16, MA1, MB1, Epi1>(g1, (lds_u8*)stages, (lds_f32*)row_scale, (lds_i32*)&next_tile);
   __syncthreads();
-  gemm_v3_body<E2, MA2, MB2, KB2, Epi2>(g2, (lds_u8*)stages, (lds_f32*)row_scale, (lds_u32*)code_lut,
-                                         (lds_i32*)&next_tile);
+  gemm_v3_body<EBF16, MA2, MB2, Epi2>(g2, (lds_u8*)stages, (lds_f32*)row_scale, (lds_i32*)&next_tile);
 }
 
 }  // namespace v3
@@ -1025,56 +1187,6 @@ __device__ __forceinline__ int seg_of_block(const SegTab& t) {
   int s = 0;
   while (s + 1 < t.n && (int)blockIdx.x >= t.b0[s + 1]) ++s;
   return s;
-}
-
-// Packed ternary codes q [d_out][d_in / 4 bytes] -> the B operand of dX in
-// packed form: row k (input feature) holds the codes of column k of q in
-// steps of 64 output features, 16 bytes per step (ld = 16 ceil(d_out / 64)).
-// Within a step, codes n = 64 st + 16 kk + 8 h + e go to 16-bit word kk of
-// the 8-byte half h (e at bits 2 e), the halves swapped when bit 4 of k is
-// set (the GEMM reads a lane's half with one 8-byte LDS read, free of bank
-// conflicts).  Past d_out the code is 1 (zero).
-struct TpTab {
-  const uint8_t* src[MAXG];
-  uint8_t* dst[MAXG];
-  int32_t d_out[MAXG], d_in[MAXG];
-  int32_t b0[MAXG + 1];
-  int32_t n;
-};
-
-__global__ __launch_bounds__(256) void pack_codes_t_kernel(const TpTab tab) {
-  int s = 0;
-  while (s + 1 < tab.n && (int)blockIdx.x >= tab.b0[s + 1]) ++s;
-  const int d_out = tab.d_out[s], d_in = tab.d_in[s];
-  const int n16 = d_in / 16, nst = (d_out + 63) / 64;
-  const int64_t t = (int64_t)(blockIdx.x - tab.b0[s]) * 256 + threadIdx.x;
-  if (t >= (int64_t)n16 * nst) return;
-  const int j16 = (int)(t % n16), st = (int)(t / n16);   // 16 input features, one step
-  const uint8_t* src = tab.src[s] + 4 * j16;
-  const int ldw = d_in / 4;
-  uint32_t out[16][4];
-#pragma unroll
-  for (int jj = 0; jj < 16; ++jj)
-#pragma unroll
-    for (int w = 0; w < 4; ++w) out[jj][w] = 0;
-#pragma unroll
-  for (int e = 0; e < 64; ++e) {
-    const int r = st * 64 + e;
-    const uint32_t w = r < d_out ? *reinterpret_cast<const uint32_t*>(src + (int64_t)r * ldw) : 0x55555555u;
-    const int kk = e >> 4, hh = (e >> 3) & 1, ee = e & 7;
-    const int word = 2 * hh + (kk >> 1);                  // dword of the 16 bytes
-    const int shift = 16 * (kk & 1) + 2 * ee;
-#pragma unroll
-    for (int jj = 0; jj < 16; ++jj) out[jj][word] |= ((w >> (2 * jj)) & 3u) << shift;
-  }
-  const int ldq = 16 * nst;
-  const bool swap = (j16 & 1) != 0;                        // bit 4 of k = 16 j16 + jj
-#pragma unroll
-  for (int jj = 0; jj < 16; ++jj) {
-    const uint4 v = swap ? make_uint4(out[jj][2], out[jj][3], out[jj][0], out[jj][1])
-                         : make_uint4(out[jj][0], out[jj][1], out[jj][2], out[jj][3]);
-    *reinterpret_cast<uint4*>(tab.dst[s] + (int64_t)(16 * j16 + jj) * ldq + 16 * st) = v;
-  }
 }
 
 // Packed ternary codes -> one operand byte (int8 or e4m3) per weight, same
@@ -1166,7 +1278,7 @@ __global__ __launch_bounds__(256) void unpack_int3_kernel(const SegTab tab) {
 }
 
 // int8 codes -> bf16 (|q| <= 128 is exact in bf16).
-// Weights q [d_out][d_in] (packed ternary codes, or int8) -> the B operand of
+// Weights q [d_out][d_in] (3-bit, 4-bit or 8-bit codes) -> the B operand of
 // dX with the reduction contiguous: W~T[k][n] = bf16(q[n][k]), rows of d_out
 // elements.  One 64 x 64 tile per block, transposed through LDS.
 struct TrTab {
@@ -1192,11 +1304,7 @@ __global__ __launch_bounds__(256) void unpack_t_kernel(const TrTab tab) {
     const int n = n0 + nl, k = k0 + kl;
     uint16_t v[16];
     if (n < d_out && k < d_in) {
-      if constexpr (CF == CF_T2) {
-        const uint32_t w = *reinterpret_cast<const uint32_t*>(tab.src[s] + (int64_t)n * (d_in / 4) + k / 4);
-#pragma unroll
-        for (int e = 0; e < 16; ++e) v[e] = (uint16_t)code_to_bf16_bits((w >> (2 * e)) & 3u);
-      } else if constexpr (CF == CF_I3) {
+      if constexpr (CF == CF_I3) {
         // 16 weights: 6 bytes at 3 k / 8 (k a multiple of 16: 2-byte aligned)
         const uint16_t* w3 = reinterpret_cast<const uint16_t*>(tab.src[s] + (int64_t)n * (3 * d_in / 8) + 3 * k / 8);
         const uint64_t bits = (uint64_t)w3[0] | ((uint64_t)w3[1] << 16) | ((uint64_t)w3[2] << 32);
@@ -1475,7 +1583,7 @@ __global__ __launch_bounds__(64) void sched_clear_kernel(int* sched) {
 // Tile counts and longest-first order of a group; `slot` picks its 64 bytes
 // of tile counters among the workspace's first 128.  Returns the most tiles
 // any XCD's list holds.
-template <int ELEM, int KB, class Epi>
+template <int ELEM, class Epi>
 static int32_t prep_group(Group<Epi>& grp, uint8_t* ws, int slot) {
   grp.sched = reinterpret_cast<int*>(ws + 64 * slot);
   constexpr int64_t BK = KB / (ELEM == EBF16 ? 2 : 1);
@@ -1506,31 +1614,31 @@ static int32_t prep_group(Group<Epi>& grp, uint8_t* ws, int slot) {
 
 // Persistent grid over one group: 8 x (blocks per XCD), one block per
 // compute unit at most.
-template <int ELEM, int MA, int MB, int KB, class Epi>
+template <int ELEM, int MA, int MB, class Epi>
 static hipError_t launch_group(Group<Epi>& grp, uint8_t* ws, hipStream_t s) {
-  const int32_t per_xcd = prep_group<ELEM, KB>(grp, ws, 0);
+  const int32_t per_xcd = prep_group<ELEM>(grp, ws, 0);
   if (per_xcd == 0) return hipSuccess;
   const int32_t bpx = std::min(per_xcd, std::max(1, current_device_cus() / 8));
   LaunchStatus st;
   st << launch_kernel(sched_clear_kernel, dim3(1), dim3(64), s, reinterpret_cast<int*>(ws));
   st << timed_launch(s, [&] {
-    return launch_kernel(gemm_v3_kernel<ELEM, MA, MB, KB, Epi>, dim3((unsigned)(8 * bpx)), dim3(NTH), s, grp);
+    return launch_kernel(gemm_v3_kernel<ELEM, MA, MB, Epi>, dim3((unsigned)(8 * bpx)), dim3(NTH), s, grp);
   });
   return st.e;
 }
 
 // Groups g1 then g2 in one launch (tile counters in slots 1 and 0).
-template <int E1, int MA1, int MB1, int KB1, class Epi1, int E2, int MA2, int MB2, int KB2, class Epi2>
+template <int MA1, int MB1, class Epi1, int MA2, int MB2, class Epi2>
 static hipError_t launch_dual(Group<Epi1>& g1, Group<Epi2>& g2, uint8_t* ws, hipStream_t s) {
-  const int32_t p1 = prep_group<E1, KB1>(g1, ws, 1);
-  const int32_t p2 = prep_group<E2, KB2>(g2, ws, 0);
+  const int32_t p1 = prep_group<EBF16>(g1, ws, 1);
+  const int32_t p2 = prep_group<EBF16>(g2, ws, 0);
   const int32_t per_xcd = std::max(p1, p2);
   if (per_xcd == 0) return hipSuccess;
   const int32_t bpx = std::min(per_xcd, std::max(1, current_device_cus() / 8));
   LaunchStatus st;
   st << launch_kernel(sched_clear_kernel, dim3(1), dim3(64), s, reinterpret_cast<int*>(ws));
   st << timed_launch(s, [&] {
-    return launch_kernel(gemm_v3_dual_kernel<E1, MA1, MB1, KB1, Epi1, E2, MA2, MB2, KB2, Epi2>,
+    return launch_kernel(gemm_v3_dual_kernel<MA1, MB1, Epi1, MA2, MB2, Epi2>,
                          dim3((unsigned)(8 * bpx)), dim3(NTH), s, g1, g2);
   });
   return st.e;
@@ -1539,34 +1647,6 @@ static hipError_t launch_dual(Group<Epi1>& g1, Group<Epi2>& g2, uint8_t* ws, hip
 }  // namespace v3
 
 using namespace v3;
-
-// reduction bytes per step of the unpacked 8-bit forward and of the bf16
-// backward products (128: full lines, two stages; 64: half lines, four
-// stages in flight: 9-11 % slower for the int8 forward on the LLaMA-block
-// shapes; the backward's SR epilogue needs a whole 64 KB stage for its
-// staging)
-#ifndef KB_FWD
-#define KB_FWD 128
-#endif
-#ifndef KB_BWD
-#define KB_BWD 128
-#endif
-// ternary weights against e4m3 activations: B as FP4 values (1) or as e4m3
-// bytes (0) in the scaled MFMA
-#ifndef FWD_FP4B
-#define FWD_FP4B 1
-#endif
-#ifndef DX_PACKED_B
-#define DX_PACKED_B 0
-#endif
-// dW with the SR update formed transposed (X~^T dY, EpiSR<CF, true>): 1, or
-// as dY^T X~ (0)
-#ifndef DW_TRANS
-#define DW_TRANS 1
-#endif
-#ifndef UNPACK_T2_STRIP
-#define UNPACK_T2_STRIP 1
-#endif
 
 static size_t align256(size_t n) { return (n + 255) / 256 * 256; }
 
@@ -1721,13 +1801,13 @@ hipError_t launch_fwd_batch(const BatchCfg& c, const LinearIO* io, uint8_t* ws, 
     p.nbz = 1;
   }
   if (packed) {
-    if (c.act_e4m3) st << launch_group<FWD_FP4B ? EF4B : EF8, KC, KCP, 128>(grp, ws, stream);
-    else st << launch_group<EI8, KC, KCP, 128>(grp, ws, stream);
+    if (c.act_e4m3) st << launch_group<EF4B, KC, KCP>(grp, ws, stream);
+    else st << launch_group<EI8, KC, KCP>(grp, ws, stream);
   } else if (fp4) {
-    st << launch_group<EF4B, KC, KF4, 128>(grp, ws, stream);
+    st << launch_group<EF4B, KC, KF4>(grp, ws, stream);
   } else {
-    if (c.act_e4m3) st << launch_group<EF8, KC, KC, KB_FWD>(grp, ws, stream);
-    else st << launch_group<EI8, KC, KC, KB_FWD>(grp, ws, stream);
+    if (c.act_e4m3) st << launch_group<EF8, KC, KC>(grp, ws, stream);
+    else st << launch_group<EI8, KC, KC>(grp, ws, stream);
   }
   return st.e;
 }
@@ -1819,26 +1899,6 @@ static void prep_dx(const BatchCfg& c, const LinearIO* io, uint8_t* ws, const Bw
     p.split_len = io[l].d_out;
     p.nbz = 1;
   }
-  if (c.w_ternary && DX_PACKED_B) {
-    // codes stay packed: transposed into 16-byte steps, expanded in the GEMM
-    // (fewer bytes per step, but the table expansion costs more than the
-    // copies it saves in the current main loop)
-    TpTab tab{};
-    tab.n = c.n;
-    int32_t blocks = 0;
-    for (int l = 0; l < c.n; ++l) {
-      tab.src[l] = static_cast<const uint8_t*>(io[l].Wq);
-      tab.dst[l] = ws + P.q_off[l];
-      tab.d_out[l] = (int32_t)io[l].d_out;
-      tab.d_in[l] = (int32_t)io[l].d_in;
-      tab.b0[l] = blocks;
-      blocks += (int32_t)(((io[l].d_in / 16) * ((io[l].d_out + 63) / 64) + 255) / 256);
-      grp.p[l].B = Opnd{ws + P.q_off[l], 16 * ((io[l].d_out + 63) / 64), io[l].d_in};
-    }
-    tab.b0[c.n] = blocks;
-    st << launch_kernel(pack_codes_t_kernel, dim3((unsigned)blocks), dim3(256), stream, tab);
-    return;
-  }
   // bf16 weights transposed (reduction contiguous), so both operands are
   // read without the transposing LDS reads
   TrTab tab{};
@@ -1852,15 +1912,13 @@ static void prep_dx(const BatchCfg& c, const LinearIO* io, uint8_t* ws, const Bw
     tab.tn[l] = (int32_t)((io[l].d_out + 63) / 64);
     tab.b0[l] = blocks;
     // ternary: strips of 512 reduction elements; else 64 x 64 tiles
-    const int kspan = c.w_ternary && UNPACK_T2_STRIP ? 512 : 64;
+    const int kspan = c.w_ternary ? 512 : 64;
     blocks += tab.tn[l] * (int32_t)((io[l].d_in + kspan - 1) / kspan);
     grp.p[l].B = Opnd{ws + P.q_off[l], io[l].d_out * 2, io[l].d_in};
   }
   tab.b0[c.n] = blocks;
-  if (c.w_ternary && UNPACK_T2_STRIP)
+  if (c.w_ternary)
     st << launch_kernel(unpack_t2_strip_kernel, dim3(blocks), dim3(256), stream, tab);
-  else if (c.w_ternary)
-    st << launch_kernel(unpack_t_kernel<CF_T2>, dim3(blocks), dim3(256), stream, tab);
   else if (c.w_int4)
     st << launch_kernel(unpack_t_kernel<CF_I4>, dim3(blocks), dim3(256), stream, tab);
   else if (c.w_int3)
@@ -1875,8 +1933,7 @@ hipError_t launch_dx_batch(const BatchCfg& c, const LinearIO* io, uint8_t* ws, c
   Group<EpiScale> grp{};
   LaunchStatus st;
   prep_dx(c, io, ws, P, stream, grp, st);
-  if (c.w_ternary && DX_PACKED_B) st << launch_group<EBF16, KC, KCP, 128>(grp, ws, stream);
-  else st << launch_group<EBF16, KC, KC, KB_BWD>(grp, ws, stream);
+  st << launch_group<EBF16, KC, KC>(grp, ws, stream);
   return st.e;
 }
 
@@ -1974,7 +2031,7 @@ hipError_t launch_dw_batch(const BatchCfg& c, const LinearIO* io, uint8_t* ws, c
   Group<EpiPartial> grp{};
   LaunchStatus st;
   prep_dw(c, io, ws, P, stream, grp, st);
-  st << launch_group<EBF16, KM, KC, KB_BWD>(grp, ws, stream);
+  st << launch_group<EBF16, KM, KC>(grp, ws, stream);
   if (st.e != hipSuccess) return st.e;
   return reduce_dw(c, io, ws, P, stream);
 }
@@ -1985,7 +2042,7 @@ hipError_t launch_dw_batch(const BatchCfg& c, const LinearIO* io, uint8_t* ws, c
 hipError_t launch_dxdw_batch(const BatchCfg& c, const LinearIO* io, uint8_t* ws, const BwdPlan& P,
                              hipStream_t stream) {
   if (c.n == 0) return hipSuccess;
-  if (c.M == 0 || (c.w_ternary && DX_PACKED_B)) {
+  if (c.M == 0) {
     const hipError_t e = launch_dx_batch(c, io, ws, P, stream);
     return e != hipSuccess ? e : launch_dw_batch(c, io, ws, P, stream);
   }
@@ -1996,7 +2053,7 @@ hipError_t launch_dxdw_batch(const BatchCfg& c, const LinearIO* io, uint8_t* ws,
   LaunchStatus st;
   prep_dx(c, io, ws, Q, stream, gx, st);
   prep_dw(c, io, ws, Q, stream, gw, st);
-  st << launch_dual<EBF16, KM, KC, KB_BWD, EpiPartial, EBF16, KC, KC, KB_BWD, EpiScale>(gw, gx, ws, stream);
+  st << launch_dual<KM, KC, EpiPartial, KC, KC, EpiScale>(gw, gx, ws, stream);
   if (st.e != hipSuccess) return st.e;
   return reduce_dw(c, io, ws, Q, stream);
 }
@@ -2046,10 +2103,9 @@ static hipError_t launch_dw_sr_group(const BatchCfg& c, const LinearIO* io, cons
                                uint32_t step, unsigned long long* counters, uint8_t* ws,
                                const BwdPlan& P, const int* first, Group<EpiScale>* gx,
                                hipStream_t stream) {
-  constexpr bool TR = DW_TRANS != 0;
-  Group<EpiSR<CF, TR>> gw{};
+  Group<EpiSR<CF>> gw{};
   fill_dw(c, io, ws, P, first, gw, [&](int l) {
-    EpiSR<CF, TR> e;
+    EpiSR<CF> e;
     e.wq = t[l].wq;
     e.ldc = io[l].d_in / 8 * chunk_code_bytes<CF>();
     e.d_in = io[l].d_in;
@@ -2064,36 +2120,24 @@ static hipError_t launch_dw_sr_group(const BatchCfg& c, const LinearIO* io, cons
     e.counters = counters;
     return e;
   });
-  if constexpr (TR) {
-    // dW^T = X~^T dY: X~^T [d_in][Mp] (K-contiguous) as the first operand,
-    // dY [M][d_out] (K-major) as the second
-    for (int l = 0; l < c.n; ++l) {
-      Prob<EpiSR<CF, TR>>& p = gw.p[l];
-      const int64_t I = io[l].d_in, J = io[l].d_out;
-      p.A = Opnd{ws + P.xt_off[first[l]], xt_stride(c.M) * 2, I};
-      p.B = Opnd{static_cast<const uint8_t*>(io[l].dY), J * 2, J};
-      p.I = I;
-      p.J = J;
-    }
-    if (gx != nullptr)
-      return launch_dual<EBF16, KC, KM, KB_BWD, EpiSR<CF, TR>, EBF16, KC, KC, KB_BWD, EpiScale>(gw, *gx, ws, stream);
-    return launch_group<EBF16, KC, KM, KB_BWD, EpiSR<CF, TR>>(gw, ws, stream);
-  } else {
-    if (gx != nullptr)
-      return launch_dual<EBF16, KM, KC, KB_BWD, EpiSR<CF>, EBF16, KC, KC, KB_BWD, EpiScale>(gw, *gx, ws, stream);
-    return launch_group<EBF16, KM, KC, KB_BWD, EpiSR<CF>>(gw, ws, stream);
+  // dW^T = X~^T dY: X~^T [d_in][Mp] (K-contiguous) as the first operand,
+  // dY [M][d_out] (K-major) as the second
+  for (int l = 0; l < c.n; ++l) {
+    Prob<EpiSR<CF>>& p = gw.p[l];
+    const int64_t I = io[l].d_in, J = io[l].d_out;
+    p.A = Opnd{ws + P.xt_off[first[l]], xt_stride(c.M) * 2, I};
+    p.B = Opnd{static_cast<const uint8_t*>(io[l].dY), J * 2, J};
+    p.I = I;
+    p.J = J;
   }
+  if (gx != nullptr) return launch_dual<KC, KM, EpiSR<CF>, KC, KC, EpiScale>(gw, *gx, ws, stream);
+  return launch_group<EBF16, KC, KM, EpiSR<CF>>(gw, ws, stream);
 }
 
 hipError_t launch_bwd_sr_batch(const BatchCfg& c, const LinearIO* io, const SRTensor* t, uint64_t seed,
                                uint32_t step, unsigned long long* counters, bool with_dx, uint8_t* ws,
                                const BwdPlan& P, hipStream_t stream) {
   if (c.n == 0 || c.M == 0) return hipSuccess;
-  if (with_dx && c.w_ternary && DX_PACKED_B) {
-    const hipError_t e = launch_dx_batch(c, io, ws, P, stream);
-    if (e != hipSuccess) return e;
-    with_dx = false;
-  }
   BwdPlan Q = P;
   Q.splits = with_dx ? P.splits_dual : P.splits;
   const bool fused = with_dx ? P.sr_fused_dual : P.sr_fused;
@@ -2116,9 +2160,9 @@ hipError_t launch_bwd_sr_batch(const BatchCfg& c, const LinearIO* io, const SRTe
     return EpiPartial{reinterpret_cast<float*>(ws + Q.part_off[l]), J, I * J};
   });
   if (with_dx)
-    st << launch_dual<EBF16, KM, KC, KB_BWD, EpiPartial, EBF16, KC, KC, KB_BWD, EpiScale>(gw, gx, ws, stream);
+    st << launch_dual<KM, KC, EpiPartial, KC, KC, EpiScale>(gw, gx, ws, stream);
   else
-    st << launch_group<EBF16, KM, KC, KB_BWD, EpiPartial>(gw, ws, stream);
+    st << launch_group<EBF16, KM, KC, EpiPartial>(gw, ws, stream);
   if (st.e != hipSuccess) return st.e;
   return reduce_sr(c, io, t, seed, step, counters, ws, Q, stream);
 }

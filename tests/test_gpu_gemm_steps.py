@@ -1,0 +1,97 @@
+"""The persistent GEMM's main loop at the ends of its reduction: one to five
+steps, whole and ragged (the loop keeps five half-tiles of copies in flight
+and drains them over its last two or three steps), for every operand layout:
+int8, e4m3 and FP4 forward, dX (K-contiguous), dW (K-major) unfused and with
+the SR update.  Rows and columns past one tile, ragged in both directions.
+int8 is exact; the rest is bounded by fp32 sums of exact products, 1e-3 of
+sum |terms|, as every product of the library."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import dqt_oracle as O
+from paper_2412_04787_amd import dqt, workloads as W
+from tests import gpu_util as G
+
+pytestmark = pytest.mark.gpu
+
+GRID = {"ternary": (-1, 1), "i3": (-4, 3), "i4": (-8, 7), "i8": (-127, 127)}
+
+
+def _bf16(a):
+    return torch.from_numpy(a.astype(np.float32)).to(torch.bfloat16).float().numpy().astype(np.float64)
+
+
+@pytest.mark.parametrize("d_in", [16, 128, 144, 256, 272, 384, 400, 512, 656])
+@pytest.mark.parametrize("wfmt,act,M,d_out", [
+    ("i8", "i8", 256 * 385 - 3, 16), ("ternary", "i8", 256 * 513 - 3, 16),
+    ("i4", "e4m3", 801, 272), ("i3", "e4m3", 1030, 48)])
+def test_forward(wfmt, act, M, d_out, d_in):
+    _forward(wfmt, act, M, d_out, d_in)
+
+
+@pytest.mark.parametrize("d_in", [64, 128, 192, 256, 320, 384, 448])
+def test_forward_fp4(d_in):
+    _forward("ternary", "e4m3", 900, 272, d_in)
+
+
+def _forward(wfmt, act, M, d_out, d_in):
+    lo, hi = GRID[wfmt]
+    q = W.draw_int((d_out, d_in), lo, hi, 5, M, d_in, d_out)
+    X = W.draw_normal((M, d_in), 1.0, 5, M, d_in, 1)
+    alpha = np.float32(0.017)
+    G.log(f"fwd {wfmt} {act} M={M} {d_in}->{d_out}")
+    Xd, Xv = G.to_dev(X, "bf16")
+    _, _, Y = G.run_fwd(G.make_weight(d_out, d_in, wfmt, lo, hi, alpha), G.weight_codes_dev(q, wfmt), Xd, act, "f32")
+    torch.cuda.synchronize()
+    codes, d = O.act_quant(Xv, act)
+    a = codes.astype(np.float64) if act == "i8" else O.e4m3_decode(codes).astype(np.float64)
+    sc = (d.astype(np.float32) * alpha).astype(np.float32)[:, None]
+    acc = a @ q.T.astype(np.float64)
+    got = Y.cpu().numpy()
+    if act == "i8":
+        assert np.array_equal(got, acc.astype(np.float32) * sc)
+    else:
+        ok, bad, err = G.gemm_close(got, acc * sc, np.abs(a) @ np.abs(q.T.astype(np.float64)) * sc)
+        assert ok, (bad, err)
+
+
+# dX reduces over d_out, dW over M: both in steps of 64
+@pytest.mark.parametrize("M", [1, 63, 64, 65, 128, 130, 193, 257, 320, 321])
+@pytest.mark.parametrize("wfmt,act,d_in,d_out", [
+    ("ternary", "i8", 272, 16), ("ternary", "e4m3", 48, 64), ("i8", "i8", 16, 80), ("i4", "i8", 288, 128),
+    ("i3", "i8", 80, 144), ("i8", "i8", 272, 192), ("ternary", "i8", 64, 208), ("i4", "e4m3", 16, 336)])
+def test_backward(wfmt, act, d_in, d_out, M):
+    lo, hi = GRID[wfmt]
+    q = W.draw_int((d_out, d_in), lo, hi, 6, M, d_in, d_out)
+    X = W.draw_normal((M, d_in), 1.0, 6, M, d_in, 1)
+    dY = W.draw_normal((M, d_out), 0.01, 6, M, d_in, 2)
+    alpha = np.float32(0.011)
+    w = G.make_weight(d_out, d_in, wfmt, lo, hi, alpha, 3)
+    Wq = G.weight_codes_dev(q, wfmt)
+    codes, d = O.act_quant(X, act)
+    Xq = torch.from_numpy(np.ascontiguousarray(codes)).to(G.DEV)
+    xdq = torch.from_numpy(d.astype(np.float32)).to(G.DEV)
+    dYd, dYv = G.to_dev(dY, "bf16")
+    G.log(f"bwd {wfmt} {act} M={M} {d_in}->{d_out}")
+    dX, dW = G.run_bwd(w, Wq, Xq, act, xdq, dYd, "bf16")
+    torch.cuda.synchronize()
+    a = codes.astype(np.float32) if act == "i8" else O.e4m3_decode(codes).astype(np.float32)
+    xt = _bf16(a * d.astype(np.float32)[:, None])
+    g, qq = dYv.astype(np.float64), q.astype(np.float64)
+    ok, bad, err = G.gemm_close(dX.cpu().numpy(), float(alpha) * (g @ qq), float(alpha) * (np.abs(g) @ np.abs(qq)))
+    assert ok, ("dX", bad, err)
+    ok, bad, err = G.gemm_close(dW.cpu().numpy(), g.T @ xt, np.abs(g.T) @ np.abs(xt))
+    assert ok, ("dW", bad, err)
+    # dX of the same call alone, and dW with the SR update: the same sums, so
+    # the codes of the update of this dW
+    dX1, _ = G.run_bwd(w, Wq, Xq, act, xdq, dYd, "bf16", want_dw=False)
+    W2 = Wq.clone()
+    dqt.dqt_sr_update(w, W2, dW, 0.05, 9, 4)
+    dX2 = torch.empty_like(dX)
+    io = dqt.linear_io([dict(w=w, Wq=Wq, Xq=Xq, xdq=xdq, dY=dYd, dX=dX2)])
+    dqt.dqt_linear_bwd_sr_batch(io, M, G.act_code(act), dqt.DQT_BF16, dqt.DQT_BF16, dqt.DQT_F32, 0.05, 9, 4, None,
+                                dqt.workspace(dqt.dqt_linear_bwd_batch_workspace(io, M)))
+    torch.cuda.synchronize()
+    assert torch.equal(dX1, dX) and torch.equal(dX2, dX)
+    assert torch.equal(W2, Wq)
