@@ -263,6 +263,9 @@ dqt_status dqt_linear_bwd_batch(int32_t n, const dqt_linear_io* io, int64_t M, i
     c.w_int3 = wfmt == DQT_INT3;
     return from_hip(dqt::launch_dxdw_batch(c, L, wsb, P, s));
   }
+  // fp32 environment, small linears: both products of every linear at once
+  if (dy_t == DQT_F32 && dqt::f32_small_applies(n, L, M))
+    return from_hip(dqt::launch_bwd_f32_small(code_format(wfmt), act_q == DQT_FP8E4M3, dx_t == DQT_BF16, n, L, M, s));
   // dX for the linears that want it
   int nx = 0;
   dqt::BwdPlan Px = P;
