@@ -32,7 +32,7 @@
 //    %; raised wave priority in the compute part cost 0.5 %.
 //  * Persistent grid, one block per CU.  XCD x (workgroups are dispatched
 //    round-robin over the 8 XCDs, each with its own L2) owns a contiguous
-//    1/8 of every problem's tiles, problems sorted longest reduction first;
+//    share of every problem's tiles, problems sorted longest reduction first;
 //    its blocks take tiles from that list through an atomic counter, so a
 //    block that finishes early takes the next one (longest-first list
 //    scheduling).  Before a tile's epilogue the
@@ -117,15 +117,14 @@ struct Prob {
   Epi epi;
   int64_t I, J, R, split_len;
   int32_t nbx, nby, nbz, ntiles;
+  int32_t xb[9];               // XCD x owns tiles xb[x] .. xb[x + 1] - 1
 };
 constexpr int MAXG = 8;
 template <class Epi>
 struct Group {
   Prob<Epi> p[MAXG];
   int32_t ng;
-  // tile counters: next[x] is the next tile of XCD x's list to hand out,
-  // done[x] counts XCD x's blocks that found the list empty (the last one
-  // resets both to zero for the next launch)
+  // tile counters: sched[x] is the next tile of XCD x's list to hand out
   int* sched;
 };
 
@@ -302,13 +301,12 @@ __host__ __device__ __forceinline__ void tile_coords(int local, int nbx, int nby
   bx = in / rows;
 }
 
-// Tile j of XCD x's list: XCD x owns [x n / 8, (x + 1) n / 8) of every
-// problem's n tiles, problems in launch order.  False past the end.
+// Tile j of XCD x's list: its tiles of every problem, problems in launch
+// order.  False past the end.
 template <class Epi>
 __device__ __forceinline__ bool locate(const Group<Epi>& grp, int x, int j, int& g, int& local) {
   for (g = 0; g < grp.ng; ++g) {
-    const int n = grp.p[g].ntiles;
-    const int s0 = (x * n) >> 3, cnt = (((x + 1) * n) >> 3) - s0;
+    const int s0 = grp.p[g].xb[x], cnt = grp.p[g].xb[x + 1] - s0;
     if (j < cnt) {
       local = s0 + j;
       return true;
@@ -1181,9 +1179,18 @@ struct SegTab {
   int32_t k16[MAXG];          // 16-element chunks per row (activation dequantisation)
   int32_t b0[MAXG + 1];
   int32_t n;
+  int* sched;                 // the GEMM's tile counters to zero, or NULL
 };
 
+// The persistent GEMM's tile counters (both 64-byte slots) are zeroed by
+// block 0 of the pass before it, so a workspace needs no particular contents
+// (a launch of their own took 5 us).
+__device__ __forceinline__ void sched_clear(int* sched) {
+  if (blockIdx.x == 0 && threadIdx.x < 32) sched[threadIdx.x] = 0;
+}
+
 __device__ __forceinline__ int seg_of_block(const SegTab& t) {
+  if (t.sched != nullptr) sched_clear(t.sched);
   int s = 0;
   while (s + 1 < t.n && (int)blockIdx.x >= t.b0[s + 1]) ++s;
   return s;
@@ -1289,14 +1296,14 @@ struct TrTab {
   int32_t b0[MAXG + 1];
   int32_t n;
 };
+using TLds = uint16_t[64][72];   // a transposed tile
 template <int CF>
-__global__ __launch_bounds__(256) void unpack_t_kernel(const TrTab tab) {
+__device__ __forceinline__ void unpack_t_block(const TrTab& tab, int block, TLds& t_lds) {
   int s = 0;
-  while (s + 1 < tab.n && (int)blockIdx.x >= tab.b0[s + 1]) ++s;
-  const int tile = (int)blockIdx.x - tab.b0[s];
+  while (s + 1 < tab.n && block >= tab.b0[s + 1]) ++s;
+  const int tile = block - tab.b0[s];
   const int n0 = (tile % tab.tn[s]) * 64, k0 = (tile / tab.tn[s]) * 64;
   const int d_out = tab.d_out[s], d_in = tab.d_in[s];
-  __shared__ __attribute__((aligned(16))) uint16_t t_lds[64][72];   // [k][n]
   const int t = threadIdx.x;
   {
     // thread t: row n0 + t / 4, reduction elements k0 + 16 (t mod 4) .. + 15
@@ -1354,14 +1361,13 @@ __global__ __launch_bounds__(256) void unpack_t_kernel(const TrTab tab) {
 // eight 64 x 64 tiles are transposed through LDS in turn.  (One block per
 // tile read 16 bytes of each row's line and fetched about 4 times the code
 // bytes.)
-__global__ __launch_bounds__(256) void unpack_t2_strip_kernel(const TrTab tab) {
+using CodeLds = uint32_t[64][33];   // [row][word of 16 codes]
+__device__ __forceinline__ void unpack_t2_strip_block(const TrTab& tab, int block, TLds& t_lds, CodeLds& codes) {
   int s = 0;
-  while (s + 1 < tab.n && (int)blockIdx.x >= tab.b0[s + 1]) ++s;
-  const int strip = (int)blockIdx.x - tab.b0[s];
+  while (s + 1 < tab.n && block >= tab.b0[s + 1]) ++s;
+  const int strip = block - tab.b0[s];
   const int n0 = (strip % tab.tn[s]) * 64, ks0 = (strip / tab.tn[s]) * 512;
   const int d_out = tab.d_out[s], d_in = tab.d_in[s];
-  __shared__ uint32_t codes[64][33];                                 // [row][word of 16 codes]
-  __shared__ __attribute__((aligned(16))) uint16_t t_lds[64][72];   // [k][n]
   const int t = threadIdx.x;
   {
     // thread t: row n0 + t / 4, words 8 (t mod 4) .. + 7 of the strip
@@ -1412,15 +1418,14 @@ struct DqTab {
   int64_t M, Mp;              // tokens, and the row stride of X~T (a multiple of 64)
 };
 template <bool E4M3>
-__global__ __launch_bounds__(256) void dequant_t_kernel(const DqTab tab) {
+__device__ __forceinline__ void dequant_t_block(const DqTab& tab, int block, TLds& t_lds) {
   int s = 0;
-  while (s + 1 < tab.n && (int)blockIdx.x >= tab.b0[s + 1]) ++s;
-  const int tile = (int)blockIdx.x - tab.b0[s];
+  while (s + 1 < tab.n && block >= tab.b0[s + 1]) ++s;
+  const int tile = block - tab.b0[s];
   const int64_t M = tab.M;
   const int K = tab.K[s];
   const int64_t m0 = (int64_t)(tile % tab.tm[s]) * 64;
   const int k0 = (tile / tab.tm[s]) * 64;
-  __shared__ __attribute__((aligned(16))) uint16_t t_lds[64][72];   // [k][m]
   const int t = threadIdx.x;
   {
     // thread t: token m0 + t / 4, features k0 + 16 (t mod 4) .. + 15
@@ -1461,6 +1466,33 @@ __global__ __launch_bounds__(256) void dequant_t_kernel(const DqTab tab) {
     if (k < K && m < M)
       *reinterpret_cast<uint4*>(tab.dst[s] + (int64_t)k * tab.Mp + m) =
           *reinterpret_cast<const uint4*>(&t_lds[kl][ch * 8]);
+  }
+}
+
+// What the products of a backward call need before them, in one launch: W~T
+// for dX (the first n_tr blocks), X~T for dW, and the cleared tile counters.
+// (As three launches, backward + SR of the hidden-768 block at 8192 tokens
+// took 258 us instead of 250.)
+struct PrepTab {
+  TrTab tr;
+  DqTab dq;
+  int32_t n_tr, n_dq;
+  int* sched;
+};
+template <int CF, bool E4M3>
+__global__ __launch_bounds__(256) void bwd_prep_kernel(const PrepTab tab) {
+  __shared__ __attribute__((aligned(16))) TLds t_lds;
+  sched_clear(tab.sched);
+  const int b = (int)blockIdx.x;
+  if (b < tab.n_tr) {
+    if constexpr (CF == CF_T2) {
+      __shared__ CodeLds codes;
+      unpack_t2_strip_block(tab.tr, b, t_lds, codes);
+    } else {
+      unpack_t_block<CF>(tab.tr, b, t_lds);
+    }
+  } else {
+    dequant_t_block<E4M3>(tab.dq, b - tab.n_tr, t_lds);
   }
 }
 
@@ -1574,72 +1606,104 @@ static int32_t seal(SegTab& t) {
   return b;
 }
 
-// Zeroes the persistent GEMM's tile counters (both 64-byte slots) before
-// its launch, so a workspace needs no particular contents.
-__global__ __launch_bounds__(64) void sched_clear_kernel(int* sched) {
-  if (threadIdx.x < 32) sched[threadIdx.x] = 0;
-}
+// Zeroes the persistent GEMM's tile counters before its launch where no pass
+// that does so precedes it.
+__global__ __launch_bounds__(64) void sched_clear_kernel(int* sched) { sched_clear(sched); }
 
-// Tile counts and longest-first order of a group; `slot` picks its 64 bytes
-// of tile counters among the workspace's first 128.  Returns the most tiles
-// any XCD's list holds.
-template <int ELEM, class Epi>
-static int32_t prep_group(Group<Epi>& grp, uint8_t* ws, int slot) {
-  grp.sched = reinterpret_cast<int*>(ws + 64 * slot);
-  constexpr int64_t BK = KB / (ELEM == EBF16 ? 2 : 1);
-  int64_t steps[MAXG];
+// XCD shares of a launch's tiles: contiguous, since the tiles an XCD's
+// compute units hold at once share operand panels in its L2 only if they are
+// neighbours.  A launch of at most one tile per compute unit gives its tiles,
+// problem after problem, to the XCDs in eight equal runs (an eighth of every
+// problem each left 2-3 neighbours of a small problem, and the misses held
+// the launch at 4.4 TB/s: hidden-672 block, 8-bit codes, 1423 tokens, 249
+// tiles: backward + SR 102 -> 75 us).  A larger one gives every XCD an eighth
+// of every problem, longest reductions first, so that all eight stay equally
+// long (whole problems on fewer XCDs were 2-10 % faster where they happened
+// to balance and up to 20 % slower where not).
+struct XcdShares {
+  int64_t total, at = 0;       // tiles of the launch; shared out so far
+  int32_t cus;
+  int32_t tiles[8] = {};
+  explicit XcdShares(int64_t n) : total(n), cus(std::max(8, current_device_cus())) {}
+
+  // the shares of a problem of n tiles
+  void take(int64_t n, int32_t (&xb)[9]) {
+    for (int x = 0; x <= 8; ++x)
+      xb[x] = (int32_t)(total <= cus ? std::min(std::max(total * x / 8 - at, (int64_t)0), n) : n * x / 8);
+    at += n;
+    for (int x = 0; x < 8; ++x) tiles[x] += xb[x + 1] - xb[x];
+  }
+  // blocks per XCD: one per tile, at most one per compute unit
+  int32_t blocks() const { return std::min(*std::max_element(tiles, tiles + 8), cus / 8); }
+};
+
+template <class Epi>
+static int64_t group_tiles(Group<Epi>& grp) {
+  int64_t n = 0;
   for (int g = 0; g < grp.ng; ++g) {
     Prob<Epi>& p = grp.p[g];
     p.nbx = (int32_t)((p.J + TILE - 1) / TILE);
     p.nby = (int32_t)((p.I + TILE - 1) / TILE);
     p.ntiles = p.nbx * p.nby * p.nbz;
-    steps[g] = (std::min(p.split_len, p.R) + BK - 1) / BK;
+    n += p.ntiles;
   }
+  return n;
+}
+// Longest-first order and XCD shares of a group; `slot` picks its 64 bytes of
+// tile counters among the workspace's first 128.
+template <int ELEM, class Epi>
+static void prep_group(Group<Epi>& grp, uint8_t* ws, int slot, XcdShares& sh) {
+  grp.sched = reinterpret_cast<int*>(ws + 64 * slot);
+  constexpr int64_t BK = KB / (ELEM == EBF16 ? 2 : 1);
+  auto steps = [&](int g) { return (std::min(grp.p[g].split_len, grp.p[g].R) + BK - 1) / BK; };
   for (int a = 1; a < grp.ng; ++a)          // stable insertion sort, descending
-    for (int b = a; b > 0 && steps[b] > steps[b - 1]; --b) {
-      std::swap(steps[b], steps[b - 1]);
-      std::swap(grp.p[b], grp.p[b - 1]);
-    }
-  int32_t per_xcd = 0;
-  for (int x = 0; x < 8; ++x) {
-    int32_t c = 0;
-    for (int g = 0; g < grp.ng; ++g) {
-      const int32_t n = grp.p[g].ntiles;
-      c += ((x + 1) * n >> 3) - (x * n >> 3);
-    }
-    per_xcd = std::max(per_xcd, c);
-  }
-  return per_xcd;
+    for (int b = a; b > 0 && steps(b) > steps(b - 1); --b) std::swap(grp.p[b], grp.p[b - 1]);
+  for (int g = 0; g < grp.ng; ++g) sh.take(grp.p[g].ntiles, grp.p[g].xb);
 }
 
 // Persistent grid over one group: 8 x (blocks per XCD), one block per
 // compute unit at most.
 template <int ELEM, int MA, int MB, class Epi>
-static hipError_t launch_group(Group<Epi>& grp, uint8_t* ws, hipStream_t s) {
-  const int32_t per_xcd = prep_group<ELEM>(grp, ws, 0);
-  if (per_xcd == 0) return hipSuccess;
-  const int32_t bpx = std::min(per_xcd, std::max(1, current_device_cus() / 8));
+static hipError_t launch_group(Group<Epi>& grp, uint8_t* ws, hipStream_t s, bool cleared) {
+  XcdShares sh(group_tiles(grp));
+  if (sh.total == 0) return hipSuccess;
+  prep_group<ELEM>(grp, ws, 0, sh);
+  const int32_t bpx = sh.blocks();
   LaunchStatus st;
-  st << launch_kernel(sched_clear_kernel, dim3(1), dim3(64), s, reinterpret_cast<int*>(ws));
+  if (!cleared) st << launch_kernel(sched_clear_kernel, dim3(1), dim3(64), s, reinterpret_cast<int*>(ws));
   st << timed_launch(s, [&] {
     return launch_kernel(gemm_v3_kernel<ELEM, MA, MB, Epi>, dim3((unsigned)(8 * bpx)), dim3(NTH), s, grp);
   });
   return st.e;
 }
 
-// Groups g1 then g2 in one launch (tile counters in slots 1 and 0).
+// Groups g1 and g2 in one launch (tile counters in slots 1 and 0).
 template <int MA1, int MB1, class Epi1, int MA2, int MB2, class Epi2>
-static hipError_t launch_dual(Group<Epi1>& g1, Group<Epi2>& g2, uint8_t* ws, hipStream_t s) {
-  const int32_t p1 = prep_group<EBF16>(g1, ws, 1);
-  const int32_t p2 = prep_group<EBF16>(g2, ws, 0);
-  const int32_t per_xcd = std::max(p1, p2);
-  if (per_xcd == 0) return hipSuccess;
-  const int32_t bpx = std::min(per_xcd, std::max(1, current_device_cus() / 8));
+static hipError_t launch_dual(Group<Epi1>& g1, Group<Epi2>& g2, uint8_t* ws, hipStream_t s, bool cleared) {
+  XcdShares sh(group_tiles(g1) + group_tiles(g2));
+  if (sh.total == 0) return hipSuccess;
+  prep_group<EBF16>(g1, ws, 1, sh);
+  prep_group<EBF16>(g2, ws, 0, sh);
+  const int32_t bpx = sh.blocks();
   LaunchStatus st;
-  st << launch_kernel(sched_clear_kernel, dim3(1), dim3(64), s, reinterpret_cast<int*>(ws));
+  if (!cleared) st << launch_kernel(sched_clear_kernel, dim3(1), dim3(64), s, reinterpret_cast<int*>(ws));
+  // The group with the longest tile goes first, so that the launch ends on
+  // short tiles: with few tokens dX's tiles (reduction d_out) are longer than
+  // dW's (reduction M), and left to the end they ran with most compute units
+  // idle (backward + SR, with the merged pre-pass: hidden-2496 block, 237
+  // tokens 370 -> 230 us; hidden-2048, 256 tokens 214 -> 147 us; hidden-768,
+  // 512 tokens 86 -> 61 us).  Over many rounds of tiles the end matters
+  // little, and dW first is the better neighbour for the caches (hidden-4096,
+  // 8192 tokens, 29 rounds: 5.09 against 5.14 ms; 1024 tokens, 14 rounds: 907
+  // against 889 us).  Each order is a kernel of its own: one kernel with the
+  // order as an argument spilled more and was 1-2 % slower on large blocks.
+  constexpr int64_t kOrderRounds = 16;
+  auto longest = [](const auto& g) { return g.ng > 0 ? std::min(g.p[0].split_len, g.p[0].R) : 0; };
+  const dim3 grid((unsigned)(8 * bpx));
   st << timed_launch(s, [&] {
-    return launch_kernel(gemm_v3_dual_kernel<MA1, MB1, Epi1, MA2, MB2, Epi2>,
-                         dim3((unsigned)(8 * bpx)), dim3(NTH), s, g1, g2);
+    if (longest(g2) > longest(g1) && sh.total <= kOrderRounds * 8 * bpx)
+      return launch_kernel(gemm_v3_dual_kernel<MA2, MB2, Epi2, MA1, MB1, Epi1>, grid, dim3(NTH), s, g2, g1);
+    return launch_kernel(gemm_v3_dual_kernel<MA1, MB1, Epi1, MA2, MB2, Epi2>, grid, dim3(NTH), s, g1, g2);
   });
   return st.e;
 }
@@ -1721,6 +1785,7 @@ hipError_t launch_fwd_batch(const BatchCfg& c, const LinearIO* io, uint8_t* ws, 
   if (c.w_int3) {
     SegTab tab{};
     tab.n = c.n;
+    tab.sched = reinterpret_cast<int*>(ws);
     for (int l = 0; l < c.n; ++l) {
       tab.src[l] = io[l].Wq;
       tab.dst[l] = ws + offs[l];
@@ -1734,6 +1799,7 @@ hipError_t launch_fwd_batch(const BatchCfg& c, const LinearIO* io, uint8_t* ws, 
   } else if (c.w_int4) {
     SegTab tab{};
     tab.n = c.n;
+    tab.sched = reinterpret_cast<int*>(ws);
     for (int l = 0; l < c.n; ++l) {
       tab.src[l] = io[l].Wq;
       tab.dst[l] = ws + offs[l];
@@ -1747,6 +1813,7 @@ hipError_t launch_fwd_batch(const BatchCfg& c, const LinearIO* io, uint8_t* ws, 
   } else if (fp4) {
     SegTab tab{};
     tab.n = c.n;
+    tab.sched = reinterpret_cast<int*>(ws);
     for (int l = 0; l < c.n; ++l) {
       tab.src[l] = io[l].Wq;
       tab.dst[l] = ws + offs[l];
@@ -1763,6 +1830,7 @@ hipError_t launch_fwd_batch(const BatchCfg& c, const LinearIO* io, uint8_t* ws, 
   } else if (c.w_ternary && !packed) {
     SegTab tab{};
     tab.n = c.n;
+    tab.sched = reinterpret_cast<int*>(ws);
     for (int l = 0; l < c.n; ++l) {
       tab.src[l] = io[l].Wq;
       tab.dst[l] = ws + offs[l];
@@ -1801,13 +1869,13 @@ hipError_t launch_fwd_batch(const BatchCfg& c, const LinearIO* io, uint8_t* ws, 
     p.nbz = 1;
   }
   if (packed) {
-    if (c.act_e4m3) st << launch_group<EF4B, KC, KCP>(grp, ws, stream);
-    else st << launch_group<EI8, KC, KCP>(grp, ws, stream);
+    if (c.act_e4m3) st << launch_group<EF4B, KC, KCP>(grp, ws, stream, false);
+    else st << launch_group<EI8, KC, KCP>(grp, ws, stream, false);
   } else if (fp4) {
-    st << launch_group<EF4B, KC, KF4>(grp, ws, stream);
+    st << launch_group<EF4B, KC, KF4>(grp, ws, stream, true);
   } else {
-    if (c.act_e4m3) st << launch_group<EF8, KC, KC>(grp, ws, stream);
-    else st << launch_group<EI8, KC, KC>(grp, ws, stream);
+    if (c.act_e4m3) st << launch_group<EF8, KC, KC>(grp, ws, stream, unpacked);
+    else st << launch_group<EI8, KC, KC>(grp, ws, stream, unpacked);
   }
   return st.e;
 }
@@ -1884,10 +1952,10 @@ BwdPlan plan_bwd_batch(int n, const LinearIO* io, int64_t M) {
 }
 
 // dX[m, k] = alpha sum_n dY[m, n] q[n, k]: I = M, J = d_in, R = d_out.
-// Fills the problems of the group and launches the pre-pass that writes its
-// B operand into the workspace.
+// Fills the problems of the group and the part of the pre-pass that writes
+// its B operand into the workspace.
 static void prep_dx(const BatchCfg& c, const LinearIO* io, uint8_t* ws, const BwdPlan& P,
-                    hipStream_t stream, Group<EpiScale>& grp, LaunchStatus& st) {
+                    Group<EpiScale>& grp, PrepTab& prep) {
   grp.ng = c.n;
   for (int l = 0; l < c.n; ++l) {
     Prob<EpiScale>& p = grp.p[l];
@@ -1901,7 +1969,7 @@ static void prep_dx(const BatchCfg& c, const LinearIO* io, uint8_t* ws, const Bw
   }
   // bf16 weights transposed (reduction contiguous), so both operands are
   // read without the transposing LDS reads
-  TrTab tab{};
+  TrTab& tab = prep.tr;
   tab.n = c.n;
   int32_t blocks = 0;
   for (int l = 0; l < c.n; ++l) {
@@ -1917,31 +1985,44 @@ static void prep_dx(const BatchCfg& c, const LinearIO* io, uint8_t* ws, const Bw
     grp.p[l].B = Opnd{ws + P.q_off[l], io[l].d_out * 2, io[l].d_in};
   }
   tab.b0[c.n] = blocks;
-  if (c.w_ternary)
-    st << launch_kernel(unpack_t2_strip_kernel, dim3(blocks), dim3(256), stream, tab);
-  else if (c.w_int4)
-    st << launch_kernel(unpack_t_kernel<CF_I4>, dim3(blocks), dim3(256), stream, tab);
-  else if (c.w_int3)
-    st << launch_kernel(unpack_t_kernel<CF_I3>, dim3(blocks), dim3(256), stream, tab);
-  else
-    st << launch_kernel(unpack_t_kernel<CF_I8>, dim3(blocks), dim3(256), stream, tab);
+  prep.n_tr = blocks;
+}
+
+template <int CF>
+static hipError_t launch_prep_cf(const BatchCfg& c, const PrepTab& prep, hipStream_t stream) {
+  const dim3 grid((unsigned)(prep.n_tr + prep.n_dq));
+  if (c.act_e4m3) return launch_kernel(bwd_prep_kernel<CF, true>, grid, dim3(256), stream, prep);
+  return launch_kernel(bwd_prep_kernel<CF, false>, grid, dim3(256), stream, prep);
+}
+// The pre-pass; `cleared` tells whether it ran (and so cleared the counters).
+static hipError_t launch_prep(const BatchCfg& c, PrepTab& prep, uint8_t* ws, hipStream_t stream, bool* cleared) {
+  *cleared = prep.n_tr + prep.n_dq > 0;
+  if (!*cleared) return hipSuccess;
+  prep.sched = reinterpret_cast<int*>(ws);
+  if (c.w_ternary) return launch_prep_cf<CF_T2>(c, prep, stream);
+  if (c.w_int4) return launch_prep_cf<CF_I4>(c, prep, stream);
+  if (c.w_int3) return launch_prep_cf<CF_I3>(c, prep, stream);
+  return launch_prep_cf<CF_I8>(c, prep, stream);
 }
 
 hipError_t launch_dx_batch(const BatchCfg& c, const LinearIO* io, uint8_t* ws, const BwdPlan& P,
                            hipStream_t stream) {
   if (c.M == 0 || c.n == 0) return hipSuccess;
   Group<EpiScale> grp{};
+  PrepTab prep{};
   LaunchStatus st;
-  prep_dx(c, io, ws, P, stream, grp, st);
-  st << launch_group<EBF16, KC, KC>(grp, ws, stream);
+  bool cleared;
+  prep_dx(c, io, ws, P, grp, prep);
+  st << launch_prep(c, prep, ws, stream, &cleared);
+  st << launch_group<EBF16, KC, KC>(grp, ws, stream, cleared);
   return st.e;
 }
 
-// X~T once per distinct quantised input (the dequantising transpose
+// X~T once per distinct quantised input (the dequantising transpose of the
 // pre-pass); first[l] is the linear whose X~T linear l reads.
 static void prep_xt(const BatchCfg& c, const LinearIO* io, uint8_t* ws, const BwdPlan& P,
-                    hipStream_t stream, int* first, LaunchStatus& st) {
-  DqTab tab{};
+                    int* first, PrepTab& prep) {
+  DqTab& tab = prep.dq;
   tab.M = c.M;
   tab.Mp = xt_stride(c.M);
   int32_t blocks = 0;
@@ -1961,12 +2042,7 @@ static void prep_xt(const BatchCfg& c, const LinearIO* io, uint8_t* ws, const Bw
     }
   }
   tab.b0[tab.n] = blocks;
-  if (tab.n > 0) {
-    if (c.act_e4m3)
-      st << launch_kernel(dequant_t_kernel<true>, dim3(blocks), dim3(256), stream, tab);
-    else
-      st << launch_kernel(dequant_t_kernel<false>, dim3(blocks), dim3(256), stream, tab);
-  }
+  prep.n_dq = blocks;
 }
 
 // dW[n, k] = sum_m dY[m, n] X~T[k, m]: I = d_out, J = d_in, R = M, split over
@@ -1994,9 +2070,9 @@ static void fill_dw(const BatchCfg& c, const LinearIO* io, uint8_t* ws, const Bw
 
 // dW into dW (one split) or into the workspace partials (several).
 static void prep_dw(const BatchCfg& c, const LinearIO* io, uint8_t* ws, const BwdPlan& P,
-                    hipStream_t stream, Group<EpiPartial>& grp, LaunchStatus& st) {
+                    Group<EpiPartial>& grp, PrepTab& prep) {
   int first[kMaxBatch];
-  prep_xt(c, io, ws, P, stream, first, st);
+  prep_xt(c, io, ws, P, first, prep);
   fill_dw(c, io, ws, P, first, grp, [&](int l) {
     const int64_t I = io[l].d_out, J = io[l].d_in;
     float* target = P.splits > 1 ? reinterpret_cast<float*>(ws + P.part_off[l]) : io[l].dW;
@@ -2029,9 +2105,12 @@ hipError_t launch_dw_batch(const BatchCfg& c, const LinearIO* io, uint8_t* ws, c
                            hipStream_t stream) {
   if (c.n == 0) return hipSuccess;
   Group<EpiPartial> grp{};
+  PrepTab prep{};
   LaunchStatus st;
-  prep_dw(c, io, ws, P, stream, grp, st);
-  st << launch_group<EBF16, KM, KC>(grp, ws, stream);
+  bool cleared;
+  prep_dw(c, io, ws, P, grp, prep);
+  st << launch_prep(c, prep, ws, stream, &cleared);
+  st << launch_group<EBF16, KM, KC>(grp, ws, stream, cleared);
   if (st.e != hipSuccess) return st.e;
   return reduce_dw(c, io, ws, P, stream);
 }
@@ -2050,10 +2129,13 @@ hipError_t launch_dxdw_batch(const BatchCfg& c, const LinearIO* io, uint8_t* ws,
   Group<EpiPartial> gw{};
   BwdPlan Q = P;
   Q.splits = P.splits_dual;
+  PrepTab prep{};
   LaunchStatus st;
-  prep_dx(c, io, ws, Q, stream, gx, st);
-  prep_dw(c, io, ws, Q, stream, gw, st);
-  st << launch_dual<KM, KC, EpiPartial, KC, KC, EpiScale>(gw, gx, ws, stream);
+  bool cleared;
+  prep_dx(c, io, ws, Q, gx, prep);
+  prep_dw(c, io, ws, Q, gw, prep);
+  st << launch_prep(c, prep, ws, stream, &cleared);
+  st << launch_dual<KM, KC, EpiPartial, KC, KC, EpiScale>(gw, gx, ws, stream, cleared);
   if (st.e != hipSuccess) return st.e;
   return reduce_dw(c, io, ws, Q, stream);
 }
@@ -2102,7 +2184,7 @@ template <int CF>
 static hipError_t launch_dw_sr_group(const BatchCfg& c, const LinearIO* io, const SRTensor* t, uint64_t seed,
                                uint32_t step, unsigned long long* counters, uint8_t* ws,
                                const BwdPlan& P, const int* first, Group<EpiScale>* gx,
-                               hipStream_t stream) {
+                               bool cleared, hipStream_t stream) {
   Group<EpiSR<CF>> gw{};
   fill_dw(c, io, ws, P, first, gw, [&](int l) {
     EpiSR<CF> e;
@@ -2130,8 +2212,8 @@ static hipError_t launch_dw_sr_group(const BatchCfg& c, const LinearIO* io, cons
     p.I = I;
     p.J = J;
   }
-  if (gx != nullptr) return launch_dual<KC, KM, EpiSR<CF>, KC, KC, EpiScale>(gw, *gx, ws, stream);
-  return launch_group<EBF16, KC, KM, EpiSR<CF>>(gw, ws, stream);
+  if (gx != nullptr) return launch_dual<KC, KM, EpiSR<CF>, KC, KC, EpiScale>(gw, *gx, ws, stream, cleared);
+  return launch_group<EBF16, KC, KM, EpiSR<CF>>(gw, ws, stream, cleared);
 }
 
 hipError_t launch_bwd_sr_batch(const BatchCfg& c, const LinearIO* io, const SRTensor* t, uint64_t seed,
@@ -2142,16 +2224,19 @@ hipError_t launch_bwd_sr_batch(const BatchCfg& c, const LinearIO* io, const SRTe
   Q.splits = with_dx ? P.splits_dual : P.splits;
   const bool fused = with_dx ? P.sr_fused_dual : P.sr_fused;
   Group<EpiScale> gx{};
+  PrepTab prep{};
   LaunchStatus st;
-  if (with_dx) prep_dx(c, io, ws, Q, stream, gx, st);
+  bool cleared;
+  if (with_dx) prep_dx(c, io, ws, Q, gx, prep);
   int first[kMaxBatch];
-  prep_xt(c, io, ws, Q, stream, first, st);
+  prep_xt(c, io, ws, Q, first, prep);
+  st << launch_prep(c, prep, ws, stream, &cleared);
   if (Q.splits == 1 && fused) {
     Group<EpiScale>* const pgx = with_dx ? &gx : nullptr;
-    if (c.w_ternary) st << launch_dw_sr_group<CF_T2>(c, io, t, seed, step, counters, ws, Q, first, pgx, stream);
-    else if (c.w_int4) st << launch_dw_sr_group<CF_I4>(c, io, t, seed, step, counters, ws, Q, first, pgx, stream);
-    else if (c.w_int3) st << launch_dw_sr_group<CF_I3>(c, io, t, seed, step, counters, ws, Q, first, pgx, stream);
-    else st << launch_dw_sr_group<CF_I8>(c, io, t, seed, step, counters, ws, Q, first, pgx, stream);
+    if (c.w_ternary) st << launch_dw_sr_group<CF_T2>(c, io, t, seed, step, counters, ws, Q, first, pgx, cleared, stream);
+    else if (c.w_int4) st << launch_dw_sr_group<CF_I4>(c, io, t, seed, step, counters, ws, Q, first, pgx, cleared, stream);
+    else if (c.w_int3) st << launch_dw_sr_group<CF_I3>(c, io, t, seed, step, counters, ws, Q, first, pgx, cleared, stream);
+    else st << launch_dw_sr_group<CF_I8>(c, io, t, seed, step, counters, ws, Q, first, pgx, cleared, stream);
     return st.e;
   }
   Group<EpiPartial> gw{};
@@ -2160,9 +2245,9 @@ hipError_t launch_bwd_sr_batch(const BatchCfg& c, const LinearIO* io, const SRTe
     return EpiPartial{reinterpret_cast<float*>(ws + Q.part_off[l]), J, I * J};
   });
   if (with_dx)
-    st << launch_dual<KM, KC, EpiPartial, KC, KC, EpiScale>(gw, gx, ws, stream);
+    st << launch_dual<KM, KC, EpiPartial, KC, KC, EpiScale>(gw, gx, ws, stream, cleared);
   else
-    st << launch_group<EBF16, KM, KC, EpiPartial>(gw, ws, stream);
+    st << launch_group<EBF16, KM, KC, EpiPartial>(gw, ws, stream, cleared);
   if (st.e != hipSuccess) return st.e;
   return reduce_sr(c, io, t, seed, step, counters, ws, Q, stream);
 }

@@ -95,3 +95,41 @@ def test_backward(wfmt, act, d_in, d_out, M):
     torch.cuda.synchronize()
     assert torch.equal(dX1, dX) and torch.equal(dX2, dX)
     assert torch.equal(W2, Wq)
+
+
+@pytest.mark.parametrize("M", [70, 1200, 9000])
+def test_backward_batch_is_its_singles(M):
+    """Both orders of the two products in one launch (dX's reductions longer
+    than dW's at 70 tokens, shorter at 9000), with at most one tile per compute
+    unit (70, 1200) and with several (9000): dX of the batch is that of each
+    linear alone, bit for bit, and the fused update's codes and counts are
+    those of the update of the batch's dW."""
+    ents = []
+    for tid, (d_in, d_out) in enumerate([(272, 1040), (1040, 272), (528, 528), (16, 16)]):
+        q = W.draw_int((d_out, d_in), -1, 1, 12, M, tid)
+        X = W.draw_normal((M, d_in), 1.0, 12, M, tid, 1)
+        codes, d = O.act_quant(X, "i8")
+        w = G.make_weight(d_out, d_in, "ternary", -1, 1, 0.015, tid)
+        ents.append(dict(w=w, Wq=G.weight_codes_dev(q, "ternary"), Xq=torch.from_numpy(codes).to(G.DEV),
+                         xdq=torch.from_numpy(d.astype(np.float32)).to(G.DEV),
+                         dY=G.to_dev(W.draw_normal((M, d_out), 0.01, 12, M, tid, 2), "bf16")[0],
+                         dX=torch.empty((M, d_in), dtype=torch.bfloat16, device=G.DEV),
+                         dW=torch.empty((d_out, d_in), device=G.DEV)))
+    io = dqt.linear_io(ents)
+    ws = dqt.workspace(dqt.dqt_linear_bwd_batch_workspace(io, M))
+    bf, i8 = dqt.DQT_BF16, dqt.DQT_I8
+    dqt.dqt_linear_bwd_batch(io, M, i8, bf, bf, bf, ws)
+    torch.cuda.synchronize()
+    for e in ents:
+        dX, _ = G.run_bwd(e["w"], e["Wq"], e["Xq"], "i8", e["xdq"], e["dY"], "bf16", "bf16", want_dw=False)
+        torch.cuda.synchronize()
+        assert torch.equal(dX, e["dX"])
+    cnt, cnt2 = (torch.zeros(2, dtype=torch.int64, device=G.DEV) for _ in range(2))
+    two = [dict(e, Wq=e["Wq"].clone()) for e in ents]
+    dqt.dqt_sr_update_batch(dqt.linear_io(two), 0.02, 5, 3, cnt)
+    fused = [dict(e, dW=None, dX=torch.empty_like(e["dX"])) for e in ents]
+    dqt.dqt_linear_bwd_sr_batch(dqt.linear_io(fused), M, i8, bf, bf, bf, 0.02, 5, 3, cnt2, ws)
+    torch.cuda.synchronize()
+    for a, b, e in zip(two, fused, ents):
+        assert torch.equal(a["Wq"], b["Wq"]) and torch.equal(b["dX"], e["dX"])
+    assert torch.equal(cnt, cnt2)
