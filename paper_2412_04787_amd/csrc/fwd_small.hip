@@ -10,13 +10,14 @@
 //  * fwd_skinny_kernel: bound by the stream of codes;
 //  * fwd_mid_kernel: bound by the matrix cores and the LDS traffic of its
 //    64 x 64 wave tiles.
-// Measured, whole block with the activation quantisation (two launches, about
-// 12 us), the persistent GEMM -> these kernels, us:
+// Measured, whole block with the activation quantisation (one launch), the
+// persistent GEMM -> these kernels, us:
 //   tokens                        1        16        64       256       512       777
-//   h4096 ternary, e4m3   152 -> 25  153 -> 32  153 -> 56  157 -> 78  207 -> 131  217 -> 207
-//   h2048 4-bit, int8      86 -> 22   87 -> 24   88 -> 40   89 -> 41   91 -> 53   120 -> 80
-//   h2048 8-bit, int8      72 -> 24   73 -> 28   74 -> 39   75 -> 41   77 -> 51   106 -> 77
-//   h768 ternary, int8     40 -> 15   40 -> 15   41 -> 19   41 -> 20   41 -> 24    43 -> 25
+//   h4096 ternary, e4m3   152 -> 18  153 -> 21  153 -> 50  157 -> 73  207 -> 126  217 -> 205
+//   h2048 4-bit, int8      86 -> 15   87 -> 17   88 -> 35   89 -> 37   91 -> 49   120 -> 77
+//   h2048 8-bit, int8      72 -> 15   73 -> 22   74 -> 34   75 -> 37   77 -> 47   106 -> 73
+//   h768 ternary, int8     40 -> 14   40 -> 15   41 -> 18   41 -> 19   41 -> 24    43 -> 25
+// (14 us is two launches from the Python binding.)
 #include "gemm_common.h"
 #include "sr_rule.h"
 
@@ -189,12 +190,19 @@ template <> struct Acc4<true> { using type = f32x4; };
 // r's 64 codes at 256 i + 64 g of reduction step i, one wide load of the
 // packed codes (16 rows x 64 contiguous bytes per instruction for ternary
 // codes) that expands to the operands of four sub-steps.  The tokens' codes
-// come straight from the caches with the same lane-to-element map.  The four
-// waves of a block take every fourth step of the same rows and add their
+// come straight from the caches with the same lane-to-element map.  The eight
+// waves of a block take every eighth step of the same rows and add their
 // sums through LDS in wave order (int32: exact; fp32: a fixed order), so a
 // block's work is short and thousands of waves are in flight: what bounds
-// the kernel is the stream of codes.
-constexpr int kSkW = 4;
+// the kernel is the stream of codes and, with more tokens, the tokens' codes
+// from L2 (M / (16 RG) bytes per weight).
+//
+// RG (which no result depends on): 2; 4 where that leaves two blocks for
+// every compute unit (h4096 ternary, 8 tokens 22.7 -> 19.8 us, 48 tokens 50
+// -> 39 us; at hidden 2048 with 4-bit codes 1 token 14.5 -> 16.6 us); 1 for
+// up to 16 tokens of 8-bit codes, whose loads are four times the bytes (h2048,
+// 1 token 19.1 -> 14.6 us).
+constexpr int kSkW = 8;
 template <int CF, bool E4M3, int MT, int RG, bool VEC>
 __global__ __launch_bounds__(64 * kSkW) void fwd_skinny_kernel(const SmallTab tab) {
   using Acc = typename Acc4<E4M3>::type;
@@ -545,21 +553,35 @@ __global__ __launch_bounds__(256 * KS, 2) void fwd_mid_kernel(const SmallTab tab
   }
 }
 
+template <int CF, bool E4M3, int RG, bool VEC>
+hipError_t launch_skinny(SmallTab& tab, hipStream_t stream) {
+  int32_t blocks = 0;
+  for (int s = 0; s < tab.n; ++s) {
+    tab.b0[s] = blocks;
+    blocks += (tab.p[s].N + 16 * RG - 1) / (16 * RG);
+  }
+  tab.b0[tab.n] = blocks;
+  const dim3 grid((unsigned)blocks), block(64 * kSkW);
+  if (tab.M <= 16) return launch_kernel(fwd_skinny_kernel<CF, E4M3, 1, RG, VEC>, grid, block, stream, tab);
+  if constexpr (CF != CF_I8 || RG > 1) {
+    if (tab.M <= 32) return launch_kernel(fwd_skinny_kernel<CF, E4M3, 2, RG, VEC>, grid, block, stream, tab);
+    return launch_kernel(fwd_skinny_kernel<CF, E4M3, 3, RG, VEC>, grid, block, stream, tab);
+  }
+  return hipErrorInvalidValue;   // (not reached: the rule above)
+}
+
 template <int CF, bool E4M3, bool VEC>
 hipError_t launch_small_v(SmallTab& tab, hipStream_t stream) {
   return timed_launch(stream, [&] {
     if (tab.M <= kSkinnyM) {
-      constexpr int RG = 2;
-      int32_t blocks = 0;
-      for (int s = 0; s < tab.n; ++s) {
-        tab.b0[s] = blocks;
-        blocks += (tab.p[s].N + 16 * RG - 1) / (16 * RG);
+      int64_t rows = 0;
+      for (int s = 0; s < tab.n; ++s) rows += tab.p[s].N;
+      if constexpr (CF == CF_I8) {
+        if (tab.M <= 16) return launch_skinny<CF, E4M3, 1, VEC>(tab, stream);
+      } else {
+        if (rows >= 2 * 64 * current_device_cus()) return launch_skinny<CF, E4M3, 4, VEC>(tab, stream);
       }
-      tab.b0[tab.n] = blocks;
-      const dim3 grid((unsigned)blocks), block(64 * kSkW);
-      if (tab.M <= 16) return launch_kernel(fwd_skinny_kernel<CF, E4M3, 1, RG, VEC>, grid, block, stream, tab);
-      if (tab.M <= 32) return launch_kernel(fwd_skinny_kernel<CF, E4M3, 2, RG, VEC>, grid, block, stream, tab);
-      return launch_kernel(fwd_skinny_kernel<CF, E4M3, 3, RG, VEC>, grid, block, stream, tab);
+      return launch_skinny<CF, E4M3, 2, VEC>(tab, stream);
     }
     tab.mt = (tab.M + MTI - 1) / MTI;
     for (int s = 0; s < tab.n; ++s) tab.b0[s] = tab.mt * ((tab.p[s].N + MTI - 1) / MTI);
@@ -584,7 +606,8 @@ hipError_t launch_small(SmallTab& tab, bool vec, hipStream_t stream) {
 
 // The rule.  Up to kSkinnyM tokens the stream of codes is the cost, and the
 // skinny kernel's token operand traffic grows with the tokens: at 48 tokens
-// it and the mid kernel meet (h4096 58 and 56 us, h768 15 and 19 us).  The
+// it and the mid kernel meet (h2048 4-bit 64 tokens 33 and 35 us, h768 15 and
+// 18 us, h4096 over 48 tokens the mid kernel is level).  The
 // mid kernel meets the persistent GEMM where that one's tiles fill the
 // compute units twice: with int8 activations at about 512 of its 256 x 256
 // tiles (h2048 4-bit: 504 tiles 128 against 137 us, 672 tiles 171 against
