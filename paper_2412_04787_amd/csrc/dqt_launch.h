@@ -160,7 +160,9 @@ hipError_t launch_fwd_batch(const BatchCfg& c, const LinearIO* io, uint8_t* ws, 
 // (fwd_small.hip; the rule with its measurements stands there): a streaming
 // kernel up to kSkinnyM tokens; 128 x 128 tiles above, with the reduction in
 // two halves up to kMidSplitM tokens.
-constexpr int64_t kSkinnyM = 48;
+constexpr int64_t kSkinnyM = 64;
+constexpr int64_t kSkinnyM8 = 48;       // ... with 8-bit codes,
+constexpr int64_t kSkinnyM8Wide = 16;   //     and with 8-bit codes in many rows
 constexpr int64_t kMidSplitM = 256;
 constexpr int64_t kMidMaxE4M3 = 800;    // tokens
 constexpr int64_t kMidMaxTiles = 512;   // 256 x 256 output tiles of the batch

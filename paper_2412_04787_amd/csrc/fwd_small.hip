@@ -565,7 +565,8 @@ hipError_t launch_skinny(SmallTab& tab, hipStream_t stream) {
   if (tab.M <= 16) return launch_kernel(fwd_skinny_kernel<CF, E4M3, 1, RG, VEC>, grid, block, stream, tab);
   if constexpr (CF != CF_I8 || RG > 1) {
     if (tab.M <= 32) return launch_kernel(fwd_skinny_kernel<CF, E4M3, 2, RG, VEC>, grid, block, stream, tab);
-    return launch_kernel(fwd_skinny_kernel<CF, E4M3, 3, RG, VEC>, grid, block, stream, tab);
+    if (tab.M <= 48) return launch_kernel(fwd_skinny_kernel<CF, E4M3, 3, RG, VEC>, grid, block, stream, tab);
+    return launch_kernel(fwd_skinny_kernel<CF, E4M3, 4, RG, VEC>, grid, block, stream, tab);
   }
   return hipErrorInvalidValue;   // (not reached: the rule above)
 }
@@ -573,13 +574,14 @@ hipError_t launch_skinny(SmallTab& tab, hipStream_t stream) {
 template <int CF, bool E4M3, bool VEC>
 hipError_t launch_small_v(SmallTab& tab, hipStream_t stream) {
   return timed_launch(stream, [&] {
-    if (tab.M <= kSkinnyM) {
-      int64_t rows = 0;
-      for (int s = 0; s < tab.n; ++s) rows += tab.p[s].N;
+    int64_t rows = 0;
+    for (int s = 0; s < tab.n; ++s) rows += tab.p[s].N;
+    const bool wide = rows >= 2 * 64 * current_device_cus();
+    if (tab.M <= (CF != CF_I8 ? kSkinnyM : wide ? kSkinnyM8Wide : kSkinnyM8)) {
       if constexpr (CF == CF_I8) {
         if (tab.M <= 16) return launch_skinny<CF, E4M3, 1, VEC>(tab, stream);
       } else {
-        if (rows >= 2 * 64 * current_device_cus()) return launch_skinny<CF, E4M3, 4, VEC>(tab, stream);
+        if (wide) return launch_skinny<CF, E4M3, 4, VEC>(tab, stream);
       }
       return launch_skinny<CF, E4M3, 2, VEC>(tab, stream);
     }
@@ -605,9 +607,12 @@ hipError_t launch_small(SmallTab& tab, bool vec, hipStream_t stream) {
 }  // namespace
 
 // The rule.  Up to kSkinnyM tokens the stream of codes is the cost, and the
-// skinny kernel's token operand traffic grows with the tokens: at 48 tokens
-// it and the mid kernel meet (h2048 4-bit 64 tokens 33 and 35 us, h768 15 and
-// 18 us, h4096 over 48 tokens the mid kernel is level).  The
+// skinny kernel's token operand traffic grows with the tokens: at 64 tokens
+// it and the mid kernel meet (h4096 ternary 47 and 49 us, h2048 4-bit 28 and
+// 32 us, h768 13 and 16 us; h4096 4-bit 61 and 55 us); with 8-bit codes
+// at 48 (h2048 29 and 31 us), or 16 where the launch has so many rows that
+// the mid kernel fills the chip (h4096: 16 tokens 73 and 70 us, 24 tokens 93
+// and 71 us).  The
 // mid kernel meets the persistent GEMM where that one's tiles fill the
 // compute units twice: with int8 activations at about 512 of its 256 x 256
 // tiles (h2048 4-bit: 504 tiles 128 against 137 us, 672 tiles 171 against
@@ -617,13 +622,13 @@ hipError_t launch_small(SmallTab& tab, bool vec, hipStream_t stream) {
 // round differently, and a batch gives the results of its linears one by
 // one: there the rule is on the tokens alone (h4096: 777 tokens 207 against
 // 217 us, 1024 tokens 249 against 223 us).
+static bool codes8(const BatchCfg& c) { return !c.w_ternary && !c.w_int4 && !c.w_int3; }
 bool fwd_small_applies(const BatchCfg& c, const LinearIO* io) {
   if (c.M <= kSkinnyM) return true;
   if (c.act_e4m3) return c.M <= kMidMaxE4M3;
   int64_t tiles = 0;
   for (int l = 0; l < c.n; ++l) tiles += ((c.M + 255) / 256) * ((io[l].d_out + 255) / 256);
-  const bool i8 = !c.w_ternary && !c.w_int4 && !c.w_int3;
-  return tiles <= (i8 ? kMidMaxTiles8 : kMidMaxTiles);
+  return tiles <= (codes8(c) ? kMidMaxTiles8 : kMidMaxTiles);
 }
 
 hipError_t launch_fwd_small(const BatchCfg& c, const LinearIO* io, hipStream_t stream) {

@@ -8,7 +8,7 @@
 // compute units, each with a chain of load, barrier and multiply per 16
 // reduction elements: a 256 x 256 linear with 512 tokens took 42 us for dX
 // and 99 us for dW on four blocks, for 0.13 GFLOP.  Here a block owns one
-// 32 x 32 tile and its four waves take every fourth group of 16 reduction
+// 32 x 32 tile and its eight waves take every eighth group of 16 reduction
 // elements, straight from memory into registers with the next group in
 // flight; their sums are added through LDS in wave order.  Lane half h of a
 // wave holds elements 8 h .. 8 h + 7 of a group for both operands.  Bound by
@@ -17,9 +17,13 @@
 // lose more blocks than that gives.  Measured, a whole fp32 step (quantise,
 // forward, backward, SR update), 128 x 128 tiles -> 32 x 32 (64 x 64), us:
 //   256 -> 256, 512 tokens      150 -> 30 (46)
-//   512 -> 512, 2048 tokens     210 -> 61 (139)
-//   1024 -> 1024, 1024 tokens   292 -> 109 (143)
-//   1024 -> 1024, 4096 tokens   353 -> 313 (493)
+//   512 -> 512, 2048 tokens     210 -> 62 (139)
+//   1024 -> 1024, 1024 tokens   292 -> 99 (143)
+//   1024 -> 1024, 4096 tokens   353 -> 312 (493)
+// (30 us was the host's time for the three calls then; 24 us now.)  With four
+// waves a block
+// 512 -> 512 with 512 tokens took 35 us instead of 31, 672 -> 192 with 1627
+// tokens 61 instead of 47.
 #include "gemm_common.h"
 #include "sr_rule.h"
 
@@ -27,7 +31,7 @@ namespace dqt {
 
 namespace {
 
-constexpr int kW = 4;      // waves per block
+constexpr int kW = 8;      // waves per block
 constexpr int kR = 16;     // reduction elements per group
 
 // One product of a launch: C [I][J], tiles in row-major order from block b0.
@@ -161,6 +165,7 @@ __global__ __launch_bounds__(64 * kW) void gemm_f32_small_kernel(const SmallProd
     red[wave][k][lane] = f32x4{acc[4 * k], acc[4 * k + 1], acc[4 * k + 2], acc[4 * k + 3]};
   __syncthreads();
   // wave k: rows 8 k + 4 h .. + 3 of column r32
+  if (wave >= 4) return;
   f32x4 v = red[0][wave][lane];
 #pragma unroll
   for (int w = 1; w < kW; ++w)

@@ -1,6 +1,6 @@
 """Forward for few tokens: the streaming and the 128 x 128 kernels and the
 persistent GEMM on both sides of every line of the rule between them, against
-the oracle: tokens around 16, 32, 48 (streaming), 128, 256 (the reduction in
+the oracle: tokens around 16, 32, 48, 64 (streaming), 128, 256 (the reduction in
 two halves) and the last few hundred; reductions that end inside a 16-, 64-
 and 128-code step; outputs that end inside a tile.  int8 activations are
 exact; e4m3 ones within the forward's bound (fp32 sums of exact products)."""
@@ -18,7 +18,8 @@ GRID = {"ternary": (-1, 1), "i3": (-4, 3), "i4": (-8, 7), "i8": (-128, 127)}
 KINDS = [("ternary", "i8"), ("ternary", "e4m3"), ("i3", "i8"), ("i3", "e4m3"), ("i4", "i8"), ("i4", "e4m3"),
          ("i8", "i8")]
 # (M, d_in, d_out)
-SHAPES = [(1, 16, 16), (16, 272, 48), (17, 64, 32), (33, 1040, 80), (48, 704, 144), (49, 80, 272), (128, 192, 128),
+SHAPES = [(1, 16, 16), (16, 272, 48), (17, 64, 32), (33, 1040, 80), (48, 704, 144), (49, 80, 272), (64, 320, 48),
+          (65, 144, 80), (128, 192, 128),
           (129, 2064, 144), (256, 448, 160), (257, 400, 272), (513, 128, 16), (800, 336, 144), (801, 336, 144),
           (900, 320, 304)]
 
@@ -66,7 +67,7 @@ def test_int8_line_of_the_persistent_gemm(wfmt):
         _check(M // 2, 48, 272, wfmt, "i8", "f32")
 
 
-@pytest.mark.parametrize("M", [7, 40, 200, 300])
+@pytest.mark.parametrize("M", [7, 60, 200, 300])
 def test_batch_equals_singles_and_needs_only_the_counters(M):
     """Linears of different widths in one call, with the smallest workspace
     the call accepts and guard bytes after every output."""
