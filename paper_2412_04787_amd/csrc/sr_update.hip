@@ -265,7 +265,8 @@ static hipError_t launch_sr_cf(const Tab& tab, int64_t tiles, uint64_t seed, uin
                                unsigned long long* counters, unsigned long long* per_tensor,
                                hipStream_t stream) {
   const auto kern = sr_update_kernel<CF, Tab>;
-  const int64_t cap = occupancy_blocks(reinterpret_cast<const void*>(kern), 256);
+  // (a block per compute unit always fits: few tiles need no occupancy query)
+  const int64_t cap = tiles <= current_device_cus() ? tiles : occupancy_blocks(reinterpret_cast<const void*>(kern), 256);
   const unsigned blocks = (unsigned)(tiles < cap ? tiles : cap);
   return launch_kernel(kern, dim3(blocks), dim3(256), stream, tab, tiles, (uint32_t)seed,
                        (uint32_t)(seed >> 32), step, counters, per_tensor);
