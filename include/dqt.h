@@ -186,6 +186,8 @@ dqt_status dqt_rmsnorm_backward(int32_t n_dy, const void* const* dY, const void*
  * packed codes, expanded in registers, with the 256 counter bytes alone: a
  * smaller workspace than this selects that form (same results for int8
  * activations, bit for bit; within the e4m3 forward's tolerance otherwise).
+ * Few tokens run from the packed codes whatever the workspace holds; the
+ * size asked for does not depend on the tokens.
  * Depends only on the descriptor. */
 size_t dqt_linear_fwd_workspace(const dqt_weight* w);
 

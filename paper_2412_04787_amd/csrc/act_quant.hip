@@ -3,7 +3,8 @@
 // OCP e4m3 codes plus one fp32 dequantisation scale per row.
 //
 // HBM-bound: reads the row (2 or 4 B/element) once and writes 1 B/element.
-// One wave per row.  Rows of up to 64 x 24 16-byte chunks are held in
+// Few tokens: a block per row; else 16 lanes per row (up to 256 chunks of 16
+// bytes) or a wave per row.  Rows of up to 64 x 24 chunks are held in
 // registers between the absmax and the quantisation (the row is read from
 // memory once); longer rows are read twice, the second time from cache.
 // Up to kMaxBatch inputs (same M and dtypes) are quantised by one launch.
