@@ -203,20 +203,17 @@ hipError_t launch_t(SmallProds& tab, hipStream_t stream) {
 
 }  // namespace
 
-// The rule: few outputs (64 x 64 tiles of dX and dW together: 1280 of them
-// 313 against 353 us, 1536 631 against 670 us, 3072 1205 against 1065 us),
-// and a reduction over tokens that one block's waves get through (256 -> 256:
-// 512 tokens 30 against 150 us; 16384 tokens, which the 128 x 128 kernel
-// splits over blocks, 290 against 193 us).
-bool f32_small_applies(int n, const LinearIO* io, int64_t M) {
+// The rule, for each linear by its own shape: few outputs (64 x 64 tiles of dX
+// and dW together: 1280 of them 313 against 353 us, 1536 631 against 670 us,
+// 3072 1205 against 1065 us), and a reduction over tokens that one block's
+// waves get through (256 -> 256: 512 tokens 30 against 150 us; 16384 tokens,
+// which the 128 x 128 kernel splits over blocks, 290 against 193 us).  The two
+// kernels add in different orders, and a batch gives the results of its
+// linears one by one: so neither the other linears of the call nor which of
+// dX and dW it asks for count.
+bool f32_small_applies(int64_t d_in, int64_t d_out, int64_t M) {
   if (M < 1 || M > kF32SmallM) return false;
-  int64_t c = 0;
-  for (int l = 0; l < n; ++l) {
-    const int64_t tm = (M + 63) / 64, ti = (io[l].d_in + 63) / 64, to = (io[l].d_out + 63) / 64;
-    if (io[l].dX != nullptr) c += tm * ti;
-    if (io[l].dW != nullptr) c += to * ti;
-  }
-  return c <= kF32SmallTiles;
+  return ((M + 63) / 64 + (d_out + 63) / 64) * ((d_in + 63) / 64) <= kF32SmallTiles;
 }
 
 hipError_t launch_bwd_f32_small(int cf, bool e4m3, bool dx_bf16, int n, const LinearIO* io, int64_t M,

@@ -1,7 +1,8 @@
 """fp32-environment backward of small linears (32 x 32 tiles, both products in
 one launch) and the line to the 128 x 128 kernels, against float64: reductions
 inside one group of 16, one and several groups per wave and ragged tokens;
-ragged outputs; every code format; dX or dW alone; bf16 dX.  The bound is
+ragged outputs; every code format; dX or dW alone; bf16 dX; batches on both
+sides of the line against their linears one by one.  The bound is
 that of fp32 sums of R terms, |error| <= 2 (R + 2) 2^-24 sum |terms|, plus one
 bf16 rounding where dX is bf16."""
 import numpy as np
@@ -67,11 +68,22 @@ def test_line_in_tiles(d_out):
     _case(512, 4096, d_out, "i4", "i8")
 
 
-def test_batch_is_its_singles():
-    M = 50
+# (M, shapes): all small; 2560 tiles in all, each linear 384 or 512 of them;
+# one linear past the line (1600) among small ones; past the line in tokens
+BATCHES = [(50, [(64, 48), (272, 16), (32, 208)]),
+           (512, [(1024, 1024)] * 4 + [(1024, 1536)] * 2),
+           (512, [(64, 80), (4096, 1088), (272, 144)]),
+           (4097, [(48, 64), (80, 32)])]
+
+
+@pytest.mark.parametrize("M,shapes", BATCHES)
+def test_batch_is_its_singles(M, shapes):
+    """A batch gives the bits of its linears one by one, whichever of dX and
+    dW each of them asks for."""
     g = np.random.default_rng(3)
     ents, ref = [], []
-    for tid, (d_in, d_out) in enumerate([(64, 48), (272, 16), (32, 208)]):
+    for tid, (d_in, d_out) in enumerate(shapes):
+        G.log(f"f32 batch M={M} {d_in}->{d_out}")
         q = g.integers(-8, 8, size=(d_out, d_in)).astype(np.int8)
         w = G.make_weight(d_out, d_in, "i4", -8, 7, 0.02, tid)
         e = dict(w=w, Wq=G.weight_codes_dev(q, "i4"),
@@ -79,10 +91,27 @@ def test_batch_is_its_singles():
                  xdq=torch.rand(M, device=G.DEV), dY=torch.randn((M, d_out), device=G.DEV),
                  dX=torch.empty((M, d_in), device=G.DEV), dW=torch.empty((d_out, d_in), device=G.DEV))
         ents.append(e)
-        ref.append(G.run_bwd(w, e["Wq"], e["Xq"], "i8", e["xdq"], e["dY"], "f32"))
-    io = dqt.linear_io(ents)
-    dqt.dqt_linear_bwd_batch(io, M, dqt.DQT_I8, dqt.DQT_F32, dqt.DQT_F32, dqt.DQT_F32,
-                             dqt.workspace(dqt.dqt_linear_bwd_batch_workspace(io, M)))
-    torch.cuda.synchronize()
+        args = (w, e["Wq"], e["Xq"], "i8", e["xdq"], e["dY"], "f32")
+        dX, dW = G.run_bwd(*args)
+        dX1, _ = G.run_bwd(*args, want_dw=False)
+        _, dW1 = G.run_bwd(*args, dx_out=None)
+        torch.cuda.synchronize()
+        assert torch.equal(dX1, dX) and torch.equal(dW1, dW)
+        ref.append((dX, dW))
+
+    def batch(ents):
+        io = dqt.linear_io(ents)
+        dqt.dqt_linear_bwd_batch(io, M, dqt.DQT_I8, dqt.DQT_F32, dqt.DQT_F32, dqt.DQT_F32,
+                                 dqt.workspace(dqt.dqt_linear_bwd_batch_workspace(io, M)))
+        torch.cuda.synchronize()
+
+    batch(ents)
     for e, (dX, dW) in zip(ents, ref):
         assert torch.equal(e["dX"], dX) and torch.equal(e["dW"], dW)
+    # every third linear dX alone, the next dW alone, the next neither
+    part = [dict(e, dX=torch.full_like(e["dX"], 7.0) if i % 3 == 0 else None,
+                 dW=torch.full_like(e["dW"], 7.0) if i % 3 == 1 else None) for i, e in enumerate(ents)]
+    batch(part)
+    for e, (dX, dW) in zip(part, ref):
+        assert e["dX"] is None or torch.equal(e["dX"], dX)
+        assert e["dW"] is None or torch.equal(e["dW"], dW)
