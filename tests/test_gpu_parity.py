@@ -38,7 +38,11 @@ def test_rng_stream_bit_exact(lib, seed, step, tid, i0, n):
 
 # ------------------------------------------------------------ act quant
 
-@pytest.mark.parametrize("M,K", [(1, 16), (37, 272), (513, 768), (64, 11008), (5, 20480)])
+# up to 1024 tokens and 4096 chunks a row: a block per row; beyond: 16 lanes
+# per row (1025 x 272, 768), a wave per row (4096; bf16 11008), two passes
+# (fp32 11008; 20480)
+@pytest.mark.parametrize("M,K", [(1, 16), (37, 272), (513, 768), (64, 11008), (5, 20480), (1024, 4096), (1025, 272),
+                                 (1025, 768), (1025, 4096), (1024, 11008), (1025, 11008)])
 @pytest.mark.parametrize("x_t", ["f32", "bf16"])
 @pytest.mark.parametrize("act", ["i8", "e4m3"])
 def test_act_quant_bit_exact(lib, M, K, x_t, act):
@@ -96,13 +100,14 @@ def test_act_quant_rounding_at_every_tie(lib, act):
     assert np.array_equal(Xq.cpu().numpy(), want_q.view(np.uint8))
 
 
+@pytest.mark.parametrize("M", [257, 1025])
 @pytest.mark.parametrize("x_t", ["f32", "bf16"])
 @pytest.mark.parametrize("act", ["i8", "e4m3"])
-def test_act_quant_batch_matches_oracle(lib, x_t, act):
-    """Inputs of six row lengths in one call: rows of up to 256 chunks share
-    one launch whose blocks run 1, 4, 8 or 16 chunks per lane (by input),
-    longer rows take the whole-wave kernel."""
-    M = 257
+def test_act_quant_batch_matches_oracle(lib, x_t, act, M):
+    """Inputs of six row lengths in one call.  257 tokens: one launch of a
+    block per row.  1025: rows of up to 256 chunks share one launch whose
+    blocks run 1, 4, 8 or 16 chunks per lane (by input), longer rows take the
+    kernels of a wave per row."""
     Ks = [768, 2048, 272, 11008, 16, 512]
     ents, seen = [], []
     for i, K in enumerate(Ks):
@@ -173,7 +178,14 @@ def test_forward(lib, shape, kind):
         assert ok, (nbad, emax)
 
 
-PACKED_SHAPES = [(512, 256, 256), (1000, 1024, 208), (257, 320, 96), (70, 64, 80), (1, 128, 16)]
+# the last ones are past the kernels for few tokens in both formats (more than
+# 512 tiles of 256 x 256; more than 800 tokens), so the smallest workspace
+# takes the persistent GEMM's packed form: one to five steps of 128 elements,
+# whole and ragged, against its three stages, two column tiles, and more tiles
+# than compute units; (801, 192, 272) is past them with e4m3 activations only
+PACKED_SHAPES = [(512, 256, 256), (1000, 1024, 208), (257, 320, 96), (70, 64, 80), (1, 128, 16), (801, 192, 272),
+                 (256 * 257, 64, 272), (256 * 256 + 1, 192, 272), (256 * 257 - 3, 256, 272), (256 * 257, 320, 272),
+                 (256 * 257, 384, 272), (256 * 257 - 130, 576, 272)]
 
 
 @pytest.mark.parametrize("shape", PACKED_SHAPES)
@@ -182,7 +194,8 @@ def test_forward_packed_form_with_the_smallest_workspace(lib, shape, act):
     """Ternary codes with d_in a multiple of 64 given only the 256 counter
     bytes of workspace run from the packed codes, expanded in registers
     (int8 bytes, or FP4 values against e4m3 activations): int8 bit for bit
-    equal to the expanded form and the oracle, e4m3 within the tolerance."""
+    equal to the expanded form and the oracle, e4m3 within the tolerance.
+    (Few tokens or tiles take the packed codes with any workspace.)"""
     M, d_in, d_out = shape
     log(f"forward packed form M={M} d_in={d_in} d_out={d_out} {act}")
     q = _weights(d_out, d_in, "ternary", -1, 1, M, d_in, d_out, 7)
