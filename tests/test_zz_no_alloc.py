@@ -71,8 +71,10 @@ def test_noalloc_forward_matches_workspace_forward(lib, ci):
 def test_noalloc_forward_large_ternary_runs_packed(lib):
     """Ternary codes whose expansion exceeds the array (2 x 4096 x 4096 bytes
     plus the counters) run from the packed codes, expanded in registers:
-    int8 activations give the bits of the workspace call, which expands them."""
-    for k, M in enumerate((256, 96)):
+    int8 activations give the bits of the workspace call, which expands them
+    (4300 and 4097 tokens: 544 tiles of 256 x 256, past the kernels for few
+    tokens, which take the packed codes in either call: 96 tokens)."""
+    for k, M in enumerate((4300, 4097, 96)):
         log(f"no-alloc forward, packed ternary: M={M}")
         a_code, ents_ws, ents_na = _batch(M, [(4096, 4096), (4096, 4096)], "ternary", -1, 1, "i8", 70 + k)
         io_ws, io_na = dqt.linear_io(ents_ws), dqt.linear_io(ents_na)
