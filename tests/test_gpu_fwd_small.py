@@ -60,11 +60,12 @@ def test_shapes(shape, wfmt, act):
 @pytest.mark.parametrize("wfmt", list(GRID))
 def test_int8_line_of_the_persistent_gemm(wfmt):
     """The rule for int8 activations counts 256 x 256 tiles: one row tile of
-    tokens on each side of its lines (384 tiles for 8-bit codes, 512 else)."""
+    tokens on each side of its lines (384 tiles for 8-bit codes, 512 else),
+    with one column tile and with two."""
     line = 384 if wfmt == "i8" else 512
-    for M in (256 * line, 256 * line + 1):
-        _check(M, 80, 16, wfmt, "i8", "bf16")
-        _check(M // 2, 48, 272, wfmt, "i8", "f32")
+    for past in (0, 1):
+        _check(256 * line + past, 80, 16, wfmt, "i8", "bf16")
+        _check(128 * line + past, 48, 272, wfmt, "i8", "f32")
 
 
 @pytest.mark.parametrize("M", [7, 60, 200, 300])

@@ -24,9 +24,16 @@ def _bf16(a):
 
 @pytest.mark.parametrize("d_in", [16, 128, 144, 256, 272, 384, 400, 512, 656])
 @pytest.mark.parametrize("wfmt,act,M,d_out", [
-    ("i8", "i8", 256 * 385 - 3, 16), ("ternary", "i8", 256 * 513 - 3, 16),
-    ("i4", "e4m3", 801, 272), ("i3", "e4m3", 1030, 48)])
+    ("i8", "i8", 256 * 385 - 3, 16), ("ternary", "i8", 256 * 513 - 3, 16), ("i8", "i8", 256 * 193 - 3, 272),
+    ("ternary", "i8", 256 * 257 - 3, 272), ("i4", "e4m3", 801, 272), ("i3", "e4m3", 1030, 48)])
 def test_forward(wfmt, act, M, d_out, d_in):
+    _forward(wfmt, act, M, d_out, d_in)
+
+
+# more than 8 column tiles: bands of four row tiles, the last band of one
+@pytest.mark.parametrize("wfmt,act,M,d_out,d_in", [
+    ("i8", "i8", 256 * 41 - 3, 2320, 144), ("i4", "i8", 256 * 53 - 3, 2320, 272), ("ternary", "e4m3", 1030, 2320, 192)])
+def test_forward_in_bands(wfmt, act, M, d_out, d_in):
     _forward(wfmt, act, M, d_out, d_in)
 
 
