@@ -562,12 +562,15 @@ hipError_t launch_skinny(SmallTab& tab, hipStream_t stream) {
   }
   tab.b0[tab.n] = blocks;
   const dim3 grid((unsigned)blocks), block(64 * kSkW);
-  if (tab.M <= 16) return launch_kernel(fwd_skinny_kernel<CF, E4M3, 1, RG, VEC>, grid, block, stream, tab);
-  if constexpr (CF != CF_I8 || RG > 1) {
+  // (8-bit codes come with RG = 1 up to 16 tokens, with RG = 2 for 17 to 48)
+  constexpr bool k8 = CF == CF_I8;
+  if constexpr (!k8 || RG == 1)
+    if (tab.M <= 16) return launch_kernel(fwd_skinny_kernel<CF, E4M3, 1, RG, VEC>, grid, block, stream, tab);
+  if constexpr (!k8 || RG > 1) {
     if (tab.M <= 32) return launch_kernel(fwd_skinny_kernel<CF, E4M3, 2, RG, VEC>, grid, block, stream, tab);
     if (tab.M <= 48) return launch_kernel(fwd_skinny_kernel<CF, E4M3, 3, RG, VEC>, grid, block, stream, tab);
-    return launch_kernel(fwd_skinny_kernel<CF, E4M3, 4, RG, VEC>, grid, block, stream, tab);
   }
+  if constexpr (!k8) return launch_kernel(fwd_skinny_kernel<CF, E4M3, 4, RG, VEC>, grid, block, stream, tab);
   return hipErrorInvalidValue;   // (not reached: the rule above)
 }
 
