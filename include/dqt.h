@@ -88,16 +88,18 @@ typedef enum {
  *   wfmt = DQT_INT4: the n-bit grids of Eq. 3 for n <= 4 (n = 2, 3, 4:
  *          -2..1, -4..3, -8..7) in 4-bit two's-complement nibbles: weight
  *          (n, k) at byte n * (d_in / 2) + k / 2, low nibble for even k.
- *          Requires -8 <= qmin < qmax <= 7.  The forward and dX expand the
- *          nibbles to int8 or e4m3 / bf16 in the workspace; the updates work
- *          on the nibbles in place.
+ *          Requires -8 <= qmin < qmax <= 7.  The forward expands the
+ *          nibbles to int8 or e4m3 in the workspace (for few tokens in
+ *          registers), dX to bf16 in the workspace; the updates work on the
+ *          nibbles in place.
  *   wfmt = DQT_INT3: the n = 3 grid of Eq. 3 (-4..3) at 3 bits per weight:
  *          each group of 8 weights (n, 8 g .. 8 g + 7) is a 24-bit
  *          little-endian word in bytes n * (3 d_in / 8) + 3 g .. + 2, weight
  *          8 g + j at bits 3 j (two's complement).  Requires
- *          -4 <= qmin < qmax <= 3.  The forward and dX expand the fields to
- *          int8 or e4m3 / bf16 in the workspace; the updates work on the
- *          packed bytes in place.
+ *          -4 <= qmin < qmax <= 3.  The forward expands the fields to
+ *          int8 or e4m3 in the workspace (for few tokens in registers), dX to
+ *          bf16 in the workspace; the updates work on the packed bytes in
+ *          place.
  *   alpha: dequantisation scale, the weight's real value is q * alpha
  *          (alpha = 1/s, Eq. 3).  Finite and > 0.  Fixed for the life of the
  *          tensor: the library never recomputes it (Sec. 3.2 skips Eq. 2-4

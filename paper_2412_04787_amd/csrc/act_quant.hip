@@ -7,7 +7,9 @@
 // bytes) or a wave per row.  Rows of up to 64 x 24 chunks are held in
 // registers between the absmax and the quantisation (the row is read from
 // memory once); longer rows are read twice, the second time from cache.
-// Up to kMaxBatch inputs (same M and dtypes) are quantised by one launch.
+// Up to kMaxBatch inputs (same M and dtypes) are quantised by one launch (of
+// many tokens: one for the rows of up to 256 chunks, one per class of longer
+// ones).
 #include "dqt_launch.h"
 
 namespace dqt {

@@ -117,9 +117,10 @@ hipError_t launch_act_quant_batch(int n, const ActIO* io, bool x_bf16, int64_t M
 // (same dtypes, same token count M) per launch.
 constexpr int kMaxBatch = 8;
 // The first kSchedBytes of every GEMM workspace are the persistent GEMM's:
-// bytes 0-127 hold its tile counters (two 64-byte slots, cleared by a small
-// kernel before every launch), bytes 128-143 absorb epilogue stores of
-// chunks outside the output.
+// bytes 0-127 hold its tile counters (two 64-byte slots, cleared before every
+// launch by its pre-pass, or by a small kernel where there is none), bytes
+// 128-143 and 192-207 (one per slot) absorb epilogue stores of chunks outside
+// the output.
 constexpr size_t kSchedBytes = 256;
 struct LinearIO {
   int64_t d_in, d_out;

@@ -12,9 +12,10 @@
 // elements, straight from memory into registers with the next group in
 // flight; their sums are added through LDS in wave order.  Lane half h of a
 // wave holds elements 8 h .. 8 h + 7 of a group for both operands.  Bound by
-// latency and, for the larger ones, by the operand reads from the caches (a
-// tile reads 2.5 to 4 KB per 32768 flop); 64 x 64 tiles halve those reads but
-// lose more blocks than that gives.  Measured, a whole fp32 step (quantise,
+// latency and, for the larger ones, by the operand reads from the caches (per
+// 32768 flop a tile reads 2 KB of dY and 128 to 512 bytes of codes for dX, or
+// 576 bytes of Xq and scales for dW); 64 x 64 tiles halve those reads but lose
+// more blocks than that gives.  Measured, a whole fp32 step (quantise,
 // forward, backward, SR update), 128 x 128 tiles -> 32 x 32 (64 x 64), us:
 //   256 -> 256, 512 tokens      150 -> 30 (46)
 //   512 -> 512, 2048 tokens     210 -> 62 (139)

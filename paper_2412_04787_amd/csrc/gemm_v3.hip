@@ -554,7 +554,7 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
   auto stage_ptr = [&](int slot) { return smem + slot * SLOTB; };
 
   // ---- persistent loop over this block's tiles (the counters were cleared
-  // by sched_clear_kernel just before this launch)
+  // on the stream before this launch: by its pre-pass, or sched_clear_kernel)
   lds_i32& next_tile = *next_tile_p;
   int* const next_ctr = grp.sched + xcd;
   if (tid == 0) next_tile = atomicAdd(next_ctr, 1);
@@ -1284,10 +1284,9 @@ __global__ __launch_bounds__(256) void unpack_int3_kernel(const SegTab tab) {
   static_cast<uint4*>(tab.dst[s])[t] = make_uint4(o[0], o[1], o[2], o[3]);
 }
 
-// int8 codes -> bf16 (|q| <= 128 is exact in bf16).
 // Weights q [d_out][d_in] (3-bit, 4-bit or 8-bit codes) -> the B operand of
-// dX with the reduction contiguous: W~T[k][n] = bf16(q[n][k]), rows of d_out
-// elements.  One 64 x 64 tile per block, transposed through LDS.
+// dX with the reduction contiguous: W~T[k][n] = bf16(q[n][k]) (exact), rows of
+// d_out elements.  One 64 x 64 tile per block, transposed through LDS.
 struct TrTab {
   const uint8_t* src[MAXG];
   uint16_t* dst[MAXG];
@@ -1355,7 +1354,7 @@ __device__ __forceinline__ void unpack_t_block(const TrTab& tab, int block, TLds
   }
 }
 
-// Ternary codes -> W~T as unpack_t_kernel, one block per strip of 64 rows x
+// Ternary codes -> W~T as unpack_t_block, one block per strip of 64 rows x
 // 512 reduction elements: the strip's codes (whole 128-byte lines of each
 // row) come into LDS in one pass, eight loads in flight per thread, then its
 // eight 64 x 64 tiles are transposed through LDS in turn.  (One block per
@@ -2115,9 +2114,9 @@ hipError_t launch_dw_batch(const BatchCfg& c, const LinearIO* io, uint8_t* ws, c
   return reduce_dw(c, io, ws, P, stream);
 }
 
-// dW and dX of a batch in one persistent launch: dW's tiles first (the
-// longer reduction), then dX's, so compute units that draw no dW tile, or
-// finish theirs early, go on with dX at once.
+// dW and dX of a batch in one persistent launch: the tiles of one product,
+// then the other's (launch_dual has the order), so compute units that draw no
+// tile of the first, or finish theirs early, go on with the second at once.
 hipError_t launch_dxdw_batch(const BatchCfg& c, const LinearIO* io, uint8_t* ws, const BwdPlan& P,
                              hipStream_t stream) {
   if (c.n == 0) return hipSuccess;
