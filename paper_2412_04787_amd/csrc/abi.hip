@@ -263,15 +263,19 @@ dqt_status dqt_linear_bwd_batch(int32_t n, const dqt_linear_io* io, int64_t M, i
     c.w_int3 = wfmt == DQT_INT3;
     return from_hip(dqt::launch_dxdw_batch(c, L, wsb, P, s));
   }
-  // fp32 environment: both products of all small linears at once
-  bool done[DQT_MAX_BATCH] = {};
+  // fp32 environment: the small products of all linears at once
+  bool done_x[DQT_MAX_BATCH] = {}, done_w[DQT_MAX_BATCH] = {};
   if (dy_t == DQT_F32) {
     int ns = 0;
-    for (int l = 0; l < n; ++l)
-      if ((io[l].dX != nullptr || io[l].dW != nullptr) && dqt::f32_small_applies(L[l].d_in, L[l].d_out, M)) {
-        done[l] = true;
-        sub[ns++] = L[l];
-      }
+    for (int l = 0; l < n; ++l) {
+      done_x[l] = io[l].dX != nullptr && dqt::f32_small_dx(L[l].d_in, L[l].d_out, M);
+      done_w[l] = io[l].dW != nullptr && dqt::f32_small_dw(L[l].d_in, L[l].d_out, M);
+      if (!done_x[l] && !done_w[l]) continue;
+      sub[ns] = L[l];
+      if (!done_x[l]) sub[ns].dX = nullptr;
+      if (!done_w[l]) sub[ns].dW = nullptr;
+      ++ns;
+    }
     if (ns > 0)
       st = from_hip(dqt::launch_bwd_f32_small(code_format(wfmt), act_q == DQT_FP8E4M3, dx_t == DQT_BF16, ns, sub, M, s));
     if (st != DQT_OK) return st;
@@ -280,7 +284,7 @@ dqt_status dqt_linear_bwd_batch(int32_t n, const dqt_linear_io* io, int64_t M, i
   int nx = 0;
   dqt::BwdPlan Px = P;
   for (int l = 0; l < n; ++l)
-    if (io[l].dX != nullptr && !done[l]) {
+    if (io[l].dX != nullptr && !done_x[l]) {
       Px.q_off[nx] = P.q_off[l];
       sub[nx++] = L[l];
     }
@@ -321,7 +325,7 @@ dqt_status dqt_linear_bwd_batch(int32_t n, const dqt_linear_io* io, int64_t M, i
   int nw = 0;
   dqt::BwdPlan Pw = P;
   for (int l = 0; l < n; ++l)
-    if (io[l].dW != nullptr && !done[l]) {
+    if (io[l].dW != nullptr && !done_w[l]) {
       Pw.xt_off[nw] = P.xt_off[l];
       Pw.part_off[nw] = P.part_off[l];
       sub[nw++] = L[l];

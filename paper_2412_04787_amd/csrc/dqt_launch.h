@@ -191,11 +191,12 @@ hipError_t launch_dw_f32(const DwArgs& a, hipStream_t stream);
 int64_t dw_splits_f32(int64_t d_out, int64_t d_in, int64_t M);
 hipError_t launch_split_reduce(const float* ws, int splits, int64_t n, float* out, hipStream_t stream);
 // dX and dW of small linears of the fp32 environment in one launch
-// (gemm_f32_small.hip), from the codes as stored; no workspace.  The rule is
-// each linear's own.
+// (gemm_f32_small.hip), from the codes as stored; no workspace.  Each product
+// has a rule on its linear's own shape.
 constexpr int64_t kF32SmallTiles = 1536;   // 64 x 64 output tiles of dX and dW
 constexpr int64_t kF32SmallM = 4096;       // tokens
-bool f32_small_applies(int64_t d_in, int64_t d_out, int64_t M);
+bool f32_small_dx(int64_t d_in, int64_t d_out, int64_t M);
+bool f32_small_dw(int64_t d_in, int64_t d_out, int64_t M);
 hipError_t launch_bwd_f32_small(int cf, bool e4m3, bool dx_bf16, int n, const LinearIO* io, int64_t M,
                                 hipStream_t stream);
 // Direct SR update of up to kMaxBatch weight tensors (same code format) in

@@ -204,17 +204,31 @@ hipError_t launch_t(SmallProds& tab, hipStream_t stream) {
 
 }  // namespace
 
-// The rule, for each linear by its own shape: few outputs (64 x 64 tiles of dX
-// and dW together: 1280 of them 313 against 353 us, 1536 631 against 670 us,
-// 3072 1205 against 1065 us), and a reduction over tokens that one block's
-// waves get through (256 -> 256: 512 tokens 30 against 150 us; 16384 tokens,
-// which the 128 x 128 kernel splits over blocks, 290 against 193 us).  The two
-// kernels add in different orders, and a batch gives the results of its
+// The rule, for each product of a linear by the linear's own shape: few
+// outputs (64 x 64 tiles of dX and dW together: 1280 of them 313 against 353
+// us, 1536 631 against 670 us, 3072 1205 against 1065 us), and a reduction
+// over tokens that one block's waves get through (256 -> 256: 512 tokens 30
+// against 150 us; 16384 tokens, which the 128 x 128 kernel splits over blocks,
+// 290 against 193 us).  Many tiles of a reduction too short for the eight
+// waves are better in 128 x 128 (dX of 4096 -> 64: 512 tokens, 512 tiles, 12.2
+// against 15.2 us, 1000 tokens 20.3 against 16.4; dW of 16 tokens: 1024 ->
+// 1024, 256 tiles, 7.0 against 7.8 us, 2048 -> 2048 20.2 against 9.5), as are
+// those of dW with so many tokens that the other kernel splits them (1024 ->
+// 2048, 512 tiles: 1536 tokens 122 against 154 us, 4096 321 against 294).  The
+// two kernels add in different orders, and a batch gives the results of its
 // linears one by one: so neither the other linears of the call nor which of
 // dX and dW it asks for count.
-bool f32_small_applies(int64_t d_in, int64_t d_out, int64_t M) {
-  if (M < 1 || M > kF32SmallM) return false;
-  return ((M + 63) / 64 + (d_out + 63) / 64) * ((d_in + 63) / 64) <= kF32SmallTiles;
+static int64_t tiles64(int64_t rows, int64_t cols) { return ((rows + 63) / 64) * ((cols + 63) / 64); }
+static bool f32_small_linear(int64_t d_in, int64_t d_out, int64_t M) {
+  return M >= 1 && M <= kF32SmallM && tiles64(M, d_in) + tiles64(d_out, d_in) <= kF32SmallTiles;
+}
+bool f32_small_dx(int64_t d_in, int64_t d_out, int64_t M) {
+  return f32_small_linear(d_in, d_out, M) && tiles64(M, d_in) <= (d_out > 32 ? 8 * d_out : 256);
+}
+bool f32_small_dw(int64_t d_in, int64_t d_out, int64_t M) {
+  const int64_t t = tiles64(d_out, d_in);
+  return f32_small_linear(d_in, d_out, M) && t <= (M > 42 ? 6 * M : 256) &&
+         (dw_splits_f32(d_out, d_in, M) == 1 || t * M <= 3 << 18);
 }
 
 hipError_t launch_bwd_f32_small(int cf, bool e4m3, bool dx_bf16, int n, const LinearIO* io, int64_t M,

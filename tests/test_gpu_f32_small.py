@@ -68,12 +68,28 @@ def test_line_in_tiles(d_out):
     _case(512, 4096, d_out, "i4", "i8")
 
 
+# the products' own lines: 256 tiles of dX with d_out = 16, then 258; 488 with
+# d_out = 64, then 520; 256 of dW with 16 tokens, then 272; 256 tiles of dW that
+# the 128 x 128 kernel splits, with 3072 tokens, then 3088
+LINES = [(128, 8192, 16), (128, 8208, 16), (512, 3904, 64), (512, 4112, 64), (16, 1024, 1024), (16, 1024, 1040),
+         (3072, 1024, 1024), (3088, 1024, 1024)]
+
+
+@pytest.mark.parametrize("M,d_in,d_out", LINES)
+def test_line_of_each_product(M, d_in, d_out):
+    _case(M, d_in, d_out, "ternary", "i8")
+
+
 # (M, shapes): all small; 2560 tiles in all, each linear 384 or 512 of them;
-# one linear past the line (1600) among small ones; past the line in tokens
+# one linear past the line (1600) among small ones; past the line in tokens;
+# one product of a linear past its own line
 BATCHES = [(50, [(64, 48), (272, 16), (32, 208)]),
            (512, [(1024, 1024)] * 4 + [(1024, 1536)] * 2),
            (512, [(64, 80), (4096, 1088), (272, 144)]),
-           (4097, [(48, 64), (80, 32)])]
+           (4097, [(48, 64), (80, 32)]),
+           (128, [(8208, 16), (48, 64), (64, 16)]),
+           (16, [(1024, 1040), (64, 48)]),
+           (3088, [(1024, 1024), (64, 48)])]
 
 
 @pytest.mark.parametrize("M,shapes", BATCHES)
