@@ -112,9 +112,10 @@ __global__ __launch_bounds__(kWaves * kWave) void rmsnorm_bwd_kernel(
   }
 }
 
-// Rows of at most 512 NCH elements, NCH chunks of 8 per lane.
+// Rows of at most 512 NCH elements, NCH chunks of 8 per lane.  (NCH = 6: in 256
+// registers, so that two blocks fit a compute unit.)
 template <int NDY, int NCH>
-__global__ __launch_bounds__(kWaves * kWave) void rmsnorm_bwd_reg_kernel(
+__global__ __launch_bounds__(kWaves * kWave, NCH == 6 ? 2 : 1) void rmsnorm_bwd_reg_kernel(
     DyArgs dy, const uint16_t* __restrict__ X, const float* __restrict__ gamma,
     const float* __restrict__ rinv, int64_t M, int K, uint16_t* __restrict__ dX,
     float* __restrict__ gpart) {
@@ -216,9 +217,21 @@ hipError_t launch_ndy(const DyArgs& a, const uint16_t* x, const float* gamma, co
   const size_t lds = (size_t)kWaves * K * sizeof(float);
   const dim3 grid((unsigned)blocks), block(kWaves * kWave);
   const int nch = (K / 8 + kWave - 1) / kWave;
+  if constexpr (NDY == 1) {
+    // One dY over more than 2048 elements: so many blocks that they do not
+    // all fit beside each other in registers, with few rows each, are better
+    // in the kernel that keeps the gradient in LDS (1024 blocks: 1024 x 4096
+    // 15.1 against 16.1 us, 4096 x 2560 21.3 against 23.9; 4096 x 4096 42 against
+    // 35 us); two blocks a compute unit up to 3072 elements (4096 x 2064 21.7
+    // us, one 24.2; with two dY that spills, 27.5 -> 35 us).
+    if (nch > 4 && blocks > 2 * current_device_cus() && M < (int64_t)kWaves * blocks * (nch == 5 ? 2 : 1))
+      return launch_kernel_lds(rmsnorm_bwd_kernel<1>, grid, block, lds, stream, a, x, gamma, rinv, M, K, dx, gpart);
+    if (nch > 4 && nch <= 6)
+      return launch_kernel_lds(rmsnorm_bwd_reg_kernel<1, 6>, grid, block, lds, stream, a, x, gamma, rinv, M, K, dx, gpart);
+  }
   const auto k = nch <= 1 ? rmsnorm_bwd_reg_kernel<NDY, 1> : nch <= 2 ? rmsnorm_bwd_reg_kernel<NDY, 2>
-               : nch <= 4 ? rmsnorm_bwd_reg_kernel<NDY, 4> : nch <= 8 ? rmsnorm_bwd_reg_kernel<NDY, 8>
-                                                                       : rmsnorm_bwd_kernel<NDY>;
+               : nch <= 3 ? rmsnorm_bwd_reg_kernel<NDY, 3> : nch <= 4 ? rmsnorm_bwd_reg_kernel<NDY, 4>
+               : nch <= 8 ? rmsnorm_bwd_reg_kernel<NDY, 8> : rmsnorm_bwd_kernel<NDY>;
   return launch_kernel_lds(k, grid, block, lds, stream, a, x, gamma, rinv, M, K, dx, gpart);
 }
 
