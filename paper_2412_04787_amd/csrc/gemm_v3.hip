@@ -30,6 +30,10 @@
 //    reads gave 4 %, scalar base addresses 8 % (64-bit vector addresses cost
 //    issue slots and registers), reading one half-tile of B a step early 1.5
 //    %; raised wave priority in the compute part cost 0.5 %.
+//  * One-phase loop, for packed codes and for forward tiles of few steps (the
+//    rule and both sides' times stand at one_phase()): all waves run the same
+//    phase, a step's copies go out in one burst after its barrier, two stages or
+//    the three that fit with packed codes and FP4 values.
 //  * Persistent grid, one block per CU.  XCD x (workgroups are dispatched
 //    round-robin over the 8 XCDs, each with its own L2) owns a contiguous
 //    share of every problem's tiles, problems sorted longest reduction first;
@@ -171,8 +175,8 @@ __device__ __forceinline__ int opaque(int x) {
   return x;
 }
 
-// Per-thread DMA plan of one operand of one tile (the loop for packed codes):
-// the global address of each of its NL chunks at step 0; the reduction offset
+// Per-thread DMA plan of one operand of one tile (the one-phase loop): the
+// global address of each of its NL chunks at step 0; the reduction offset
 // (elements, within a step) the chunks cover, which is the same for all of
 // them; and the distance back from a chunk's address to a safe one in the
 // same row for loads past the end of the reduction.
@@ -180,7 +184,7 @@ template <int MODE, int EB>
 struct Plan {
   using G = Geo;
   static constexpr int CH = TILE * PKB / 16;   // packed 16-byte chunks per stage
-  static constexpr int NL = MODE == KCP ? CH / NTD : G::NL;
+  static constexpr int NL = MODE == KCP ? CH / NTD : MODE == KF4 ? G::NL / 2 : G::NL;
   static_assert(CH % NTD == 0, "every thread copies packed codes");
   const uint8_t* g[NL];
   int64_t back;
@@ -200,6 +204,15 @@ struct Plan {
         g[q] = o.p + gr * o.ld + r_begin / 4 + 16 * c;
         back = r_begin / 4 + 16 * c;
         rk = 64 * c;
+      } else if constexpr (MODE == KF4) {
+        // rows of 64 bytes: chunk c of row r at position c ^ ((r >> 2) & 3)
+        const int row = p >> 2;
+        const int c = (p & 3) ^ ((row >> 2) & 3);
+        int64_t gr = row0 + row;
+        if (gr > o.n - 1) gr = o.n - 1;
+        g[q] = o.p + gr * o.ld + r_begin / 2 + 16 * c;
+        back = r_begin / 2 + 16 * c;
+        rk = 32 * c;
       } else {
         const int row = p / G::CPR;
         const int c = (p % G::CPR) ^ G::swz(row);   // logical chunk (same for every q)
@@ -210,7 +223,7 @@ struct Plan {
         rk = 16 * c / EB;
       }
     }
-    inc = MODE == KC ? KB : PKB;
+    inc = MODE == KC ? KB : MODE == KF4 ? KB / 2 : PKB;
   }
 };
 
@@ -240,7 +253,7 @@ struct PPlan {
     const int64_t last = MODE == KF4 ? o.n - 16 : B32 ? o.n - 8 : o.n - 1;
     return gr < last ? gr : last;
   }
-  // this lane's distance from copy q's base
+  // this lane's distance from copy q's base (init has it in 32 bits)
   __device__ static int64_t lane_off(const Opnd& o, int64_t row0, int q, int w, int lane) {
     if constexpr (MODE == KC) {
       const int64_t rest = o.n - 1 - first_row(o, row0, q, w);   // rows of the copy past its first
@@ -261,12 +274,36 @@ struct PPlan {
   __device__ static bool wide(const Opnd& o) { return o.ld >= (int64_t)1 << 27; }
   __device__ void init(const Opnd& o, int64_t row0, int64_t r_begin, int w, int lane) {
     inc = MODE == KC ? KB : MODE == KF4 ? KB / 2 : Geo::KR * o.ld;
+    if constexpr (MODE == KM) {
+      b[0] = o.p + (r_begin + 8 * w) * o.ld + 2 * row0;
+      // (columns from the tile's first: at most 256 of them)
+      const int last = (int)(o.n - 8 - row0 < TILE ? o.n - 8 - row0 : TILE);
+      const int pc = lane & 7, k = lane >> 3;
+      const uint32_t at = (uint32_t)k * (uint32_t)o.ld;
 #pragma unroll
-    for (int q = 0; q < NB; ++q)
-      b[q] = MODE == KM ? o.p + (r_begin + 8 * w) * o.ld + 2 * row0
-                        : o.p + first_row(o, row0, q, w) * o.ld + (MODE == KF4 ? r_begin / 2 : r_begin * EB);
+      for (int q = 0; q < NV; ++q) {
+        const int col = 64 * q + 16 * ((pc >> 1) ^ (k & 3)) + 8 * (pc & 1);
+        vo[q] = at + 2u * (uint32_t)(col < last ? col : last);
+      }
+    } else {
+      int64_t fr[4];
 #pragma unroll
-    for (int q = 0; q < NV; ++q) vo[q] = (uint32_t)lane_off(o, row0, q, w, lane);
+      for (int q = 0; q < NB; ++q) {
+        fr[q] = first_row(o, row0, q, w);
+        b[q] = o.p + fr[q] * o.ld + (MODE == KF4 ? r_begin / 2 : r_begin * EB);
+      }
+      if constexpr (NV == 1) {
+        vo[0] = MODE == KF4 ? (uint32_t)(lane >> 2) * (uint32_t)o.ld + 16u * (uint32_t)chunk4(lane)
+                            : (uint32_t)(lane >> 3) * (uint32_t)o.ld + 16u * (uint32_t)chunk(w, lane);
+      } else {
+#pragma unroll
+        for (int q = 0; q < NV; ++q) {
+          const int rest = (int)(o.n - 1 - fr[q] < 7 ? o.n - 1 - fr[q] : 7);
+          const int r = (lane >> 3) < rest ? lane >> 3 : rest;
+          vo[q] = (uint32_t)r * (uint32_t)o.ld + 16u * (uint32_t)chunk(w, lane);
+        }
+      }
+    }
   }
   // reduction element (within the step) of this lane's chunk, and what takes
   // its address back to reduction element 0 of the step
@@ -321,19 +358,22 @@ using lds_u32 = __attribute__((address_space(3))) uint32_t;
 using lds_i32 = __attribute__((address_space(3))) int;
 
 // Stage geometry of one instantiation: bytes per stage and stages (two, or
-// three with packed codes).
-template <int MB>
+// in the one-phase loop the three that fit with packed codes or FP4 values).
+template <int MB, bool ONE>
 struct StageGeo {
   static constexpr int SLOTB = slot_bytes<MB>();
-  static constexpr int NS = MB == KCP ? 3 : 2;
+  static constexpr int NS = ONE && MB != KC ? 3 : 2;
   static constexpr int kBytes = NS * SLOTB;
 };
-static_assert(StageGeo<KCP>::kBytes + TILE * 4 <= 160 * 1024, "stages fit in LDS");
+static_assert(StageGeo<KCP, true>::kBytes + TILE * 4 + 16 <= 160 * 1024, "stages fit in LDS");
+static_assert(StageGeo<KF4, true>::kBytes + TILE * 4 + 16 <= 160 * 1024, "stages fit in LDS");
 
 // The persistent grouped GEMM over the tiles of `grp`, with its LDS passed
 // in (stages, 256 row factors, the next-tile slot), so that two groups can
-// run one after the other in one launch.
-template <int ELEM, int MA, int MB, class Epi>
+// run one after the other in one launch.  ONE: the one-phase loop, where all
+// waves run the same phase and a step's copies go out in one burst, for packed
+// codes and for tiles of few steps (one_phase() has the rule).
+template <int ELEM, int MA, int MB, class Epi, bool ONE = MB == KCP>
 __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem, lds_f32* row_scale,
                                              lds_i32* next_tile_p) {
   using G = Geo;
@@ -341,22 +381,21 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
   constexpr int BK = KB / EB;               // reduction elements per step
   constexpr int OPB = G::OPB;
   constexpr int NL = G::NL;
-  constexpr int SLOTB = StageGeo<MB>::SLOTB;
-  constexpr int NS = StageGeo<MB>::NS;
+  constexpr int SLOTB = StageGeo<MB, ONE>::SLOTB;
+  constexpr int NS = StageGeo<MB, ONE>::NS;
   static_assert(NW * 32 * 128 <= SLOTB, "epilogue staging (32 rows of 128 bytes per wave) fits in one stage");
-  // two loops: packed codes expanded in registers (ternary codes without a
-  // workspace for their expansion), and the two-phase loop for the rest
-  constexpr bool kPP = MB != KCP;
+  constexpr bool kPP = !ONE;
   constexpr int CB = MB == KF4 ? 1 : 2;     // copies per wave of a half-tile of B
-  static_assert(kPP || (MA == KC && (ELEM == EI8 || ELEM == EF4B)), "packed codes meet 8-bit activations");
+  static_assert(!kPP || MB != KCP, "packed codes are expanded in the one-phase loop");
+  static_assert(kPP || (MA == KC && ELEM != EBF16), "8-bit activations in the one-phase loop");
   static_assert(MB == KF4 || MB == KCP || ELEM != EF4B, "FP4 B comes from ternary codes");
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  const int wi = wave / WGC, wj = wave % WGC;
-  const int h = lane >> 5;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+  const int wi = wave_u / WGC, wj = wave_u % WGC;
+  const int h = lane >> 5;
   const int xcd = blockIdx.x & 7;
 
   // ---- state of the tile being computed
@@ -367,7 +406,7 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
     bool tail, wide;
   };
   std::conditional_t<kPP, PPlan<MA, EB, false>, Plan<KC, EB>> pa;
-  std::conditional_t<kPP, PPlan<kPP ? MB : KC, EB, true>, Plan<KCP, EB>> pb;
+  std::conditional_t<kPP, PPlan<kPP ? MB : KC, EB, true>, Plan<MB, EB>> pb;
   TileState cur;
   float my_scale = 0.0f;
 
@@ -404,20 +443,23 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
     }
   };
 
-  // (packed codes) DMA of step s of the current plans into stage `slot`
+  // (one-phase loop) DMA of step s of the current plans into stage `slot`
   auto issue = [&](int s, int slot, const TileState& T) {
     if constexpr (!kPP) {
       constexpr int NL = decltype(pa)::NL, NLB = decltype(pb)::NL;
       lds_u8* la = smem + slot * SLOTB + wave_u * 1024;
       lds_u8* lb = la + OPB;
-      const bool t = T.tail && s == T.nsteps - 1;
-      const int64_t rbase = (int64_t)s * BK;
+      // (a chunk past the end of the reduction loads the first of its row)
+      int64_t da = (int64_t)s * pa.inc, db = (int64_t)s * pb.inc;
+      if (T.tail && s == T.nsteps - 1) {
+        const int left = (int)(T.rlen - (int64_t)s * BK);
+        if (pa.rk >= left) da = -pa.back;
+        if (pb.rk >= left) db = -pb.back;
+      }
 #pragma unroll
-      for (int q = 0; q < NL; ++q)
-        dma16(t && rbase + pa.rk >= T.rlen ? pa.g[q] - pa.back : pa.g[q] + (int64_t)s * pa.inc, la + q * (NTD * 16));
+      for (int q = 0; q < NL; ++q) dma16(pa.g[q] + da, la + q * (NTD * 16));
 #pragma unroll
-      for (int q = 0; q < NLB; ++q)
-        dma16(t && rbase + pb.rk >= T.rlen ? pb.g[q] - pb.back : pb.g[q] + (int64_t)s * pb.inc, lb + q * (NTD * 16));
+      for (int q = 0; q < NLB; ++q) dma16(pb.g[q] + db, lb + q * (NTD * 16));
     }
   };
   // Half-tiles of a step (kPP): 0: A rows whose bit 6 is 0, 1: B columns of
@@ -462,18 +504,19 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
     // has no NaN and no infinity)
     if constexpr (kPP) {
     if (MB == KF4 && (w == 1 || w == 2)) return;
-    const int64_t rbase = (int64_t)s * BK;
+    const int left = (int)(T.rlen - (int64_t)s * BK);   // whole steps aside, elements of the last one
+    const int lane_s = opaque(lane);
     const i32x4 z = {0, 0, 0, 0};
+    const int rk = w == 0 || w == 3 ? pa.rk(wave_u, lane_s) : pb.rk(wave_u, lane_s);
+    if (rk >= left) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int rk = w == 0 || w == 3 ? pa.rk(wave_u, lane) : pb.rk(wave_u, lane);
-      if (rbase + rk >= T.rlen) *(__attribute__((address_space(3))) i32x4*)(half_dst(w, u, slot) + lane * 16) = z;
+      for (int u = 0; u < 2; ++u) *(__attribute__((address_space(3))) i32x4*)(half_dst(w, u, slot) + lane_s * 16) = z;
     }
     }
   };
-  // (packed codes) zero the chunks of A this thread loaded past the end of the
-  // reduction (its own DMA for that stage has completed); packed codes past
-  // the end need no zeroing: they meet zeroed A
+  // (one-phase loop) zero the chunks of A this thread loaded past the end of
+  // the reduction (its own DMA for that stage has completed); the weights
+  // there need no zeroing: they meet zeroed A, and hold no NaN or infinity
   auto zero_tail = [&](int s, int slot, const TileState& T) {
     if constexpr (!kPP) {
       lds_u8* la = smem + slot * SLOTB;
@@ -494,26 +537,41 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
   const int frow = lane & 31;
   const int t4 = (lane >> 2) & 3, u4 = lane & 3, ch = (lane >> 4) & 1;
 
-  // (packed codes) Fragments of one reduction sub-step kk (0..3; 32 bytes of
-  // reduction per tile row).  pq: this lane's 16-byte half of each B row (64
-  // codes, read once per step; sub-step kk in word kk).  Lane half h then
+  // (one-phase loop) Fragments of one reduction sub-step kk (0..3; 32 bytes of
+  // reduction per tile row).  pq, with packed codes: this lane's 16-byte half
+  // of each B row (64 codes, read once per step; sub-step kk in word kk).  Lane
+  // half h then
   // takes reduction elements 64 h .. 64 h + 63 of the step, sub-step kk the 16
   // from 64 h + 16 kk, and its A chunks follow the same order: chunk 4 h + kk
   // instead of 2 kk + h.  (One 16-byte read per row half is free of bank
   // conflicts; four 4-byte reads of words 2 kk + h, all lanes at one word
   // offset in 32-byte rows, conflicted 4-way and cost the e4m3 forward 9 %.)
   struct Frags {
-    i32x4 fa[WI];
+    i32x4 fa[WI], fb[WJ];
     uint32_t pb[WJ];          // packed codes (16 per lane), expanded at use
   };
   auto read_frags = [&](const lds_u8* la, int kk, Frags& F, const i32x4* pq) {
 #pragma unroll
     for (int t = 0; t < WI; ++t) {
       const int row = wi * 32 * WI + t * 32 + frow;
-      F.fa[t] = *(const __attribute__((address_space(3))) i32x4*)(la + row * KB + 16 * ((4 * h + kk) ^ G::swz(row)));
+      const int c = (MB == KCP ? 4 * h + kk : 2 * kk + h) ^ G::swz(row);
+      F.fa[t] = *(const __attribute__((address_space(3))) i32x4*)(la + row * KB + 16 * c);
     }
+    const lds_u8* const lb = la + OPB;
 #pragma unroll
-    for (int t = 0; t < WJ; ++t) F.pb[t] = (uint32_t)pq[t][kk];
+    for (int t = 0; t < WJ; ++t) {
+      const int row = wj * 32 * WJ + t * 32 + frow;
+      if constexpr (MB == KCP) {
+        F.pb[t] = (uint32_t)pq[t][kk];
+      } else if constexpr (MB == KF4) {
+        // sub-step pair kk / 2: lane half h takes the row's 32 values from
+        // 64 (kk / 2) + 32 h, which its e4m3 partner lanes pair them with
+        if ((kk & 1) == 0)
+          F.fb[t] = *(const __attribute__((address_space(3))) i32x4*)(lb + row * 64 + 16 * ((kk + h) ^ ((row >> 2) & 3)));
+      } else {
+        F.fb[t] = *(const __attribute__((address_space(3))) i32x4*)(lb + row * KB + 16 * ((2 * kk + h) ^ G::swz(row)));
+      }
+    }
   };
   // MFMAs of one sub-step (int8), or of two (e4m3, whose instruction reduces
   // 64 elements: sub-step pairs (0, 1) and (2, 3)).
@@ -522,18 +580,32 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
 #pragma unroll
       for (int ta = 0; ta < WI; ++ta)
 #pragma unroll
-        for (int tb = 0; tb < WJ; ++tb)
-          acc[ta][tb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(expand16(F.pb[tb], 0x000100FFu), F.fa[ta], acc[ta][tb], 0, 0, 0);
+        for (int tb = 0; tb < WJ; ++tb) {
+          const i32x4 b = MB == KCP ? expand16(F.pb[tb], 0x000100FFu) : F.fb[tb];
+          acc[ta][tb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(b, F.fa[ta], acc[ta][tb], 0, 0, 0);
+        }
     }
   };
   auto mfma2 = [&](const Frags& F0, const Frags& F1) {
-    if constexpr (!kPP && ELEM == EF4B) {
+    if constexpr (!kPP && ELEM != EI8) {
 #pragma unroll
       for (int ta = 0; ta < WI; ++ta)
 #pragma unroll
         for (int tb = 0; tb < WJ; ++tb) {
           const i32x4 a0 = F0.fa[ta], a1 = F1.fa[ta];
           const i32x8 av = {a0[0], a0[1], a0[2], a0[3], a1[0], a1[1], a1[2], a1[3]};
+          if constexpr (MB == KC) {
+            const i32x4 b0 = F0.fb[tb], b1 = F1.fb[tb];
+            const i32x8 bv = {b0[0], b0[1], b0[2], b0[3], b1[0], b1[1], b1[2], b1[3]};
+            acc[ta][tb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(bv, av, acc[ta][tb], 0, 0, 0, 127, 0, 127);
+            continue;
+          }
+          if constexpr (MB == KF4) {
+            const i32x4 f = F0.fb[tb];
+            const i32x8 bv4 = {f[0], f[1], f[2], f[3], 0, 0, 0, 0};
+            acc[ta][tb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(bv4, av, acc[ta][tb], 4, 0, 0, 127, 0, 127);
+            continue;
+          }
           // B as FP4 (format 4: 32 values in the first four registers), A
           // e4m3 (format 0), unit E8M0 scales (127 = 2^0).  With FP4 the
           // first operand's lane half h holds reduction elements 16 h ..
@@ -577,17 +649,20 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
   };
   prefetch(0);
 
-  // (packed codes) One step from stage `slot`: sub-step kk+1's fragments load
-  // while kk's MFMAs run (e4m3: sub-steps are consumed in pairs).
-  auto compute = [&](int slot) {
+  // (one-phase loop) One step from stage `slot`: sub-step kk+1's fragments load
+  // while kk's MFMAs run (e4m3: sub-steps are consumed in pairs); mid() comes
+  // after the first group of MFMAs.
+  auto compute = [&](int slot, auto&& mid) {
     const lds_u8* la = stage_ptr(slot);
     const lds_u8* lb = la + OPB;
     // (the DMA stores logical 16-byte half c of row r at half c ^ ((r >> 3) & 1))
     i32x4 pq[WJ];
+    if constexpr (MB == KCP) {
 #pragma unroll
-    for (int t = 0; t < WJ; ++t) {
-      const int row = wj * 32 * WJ + t * 32 + frow;
-      pq[t] = *(const __attribute__((address_space(3))) i32x4*)(lb + row * PKB + 16 * (h ^ ((row >> 3) & 1)));
+      for (int t = 0; t < WJ; ++t) {
+        const int row = wj * 32 * WJ + t * 32 + frow;
+        pq[t] = *(const __attribute__((address_space(3))) i32x4*)(lb + row * PKB + 16 * (h ^ ((row >> 3) & 1)));
+      }
     }
     Frags F0, F1;
     if constexpr (ELEM == EI8) {
@@ -598,6 +673,8 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
       read_frags(la, 1, F1, pq);
       __builtin_amdgcn_sched_barrier(0);
       mfma1(F0);
+      __builtin_amdgcn_sched_barrier(0);
+      mid();
       __builtin_amdgcn_sched_barrier(0);
       read_frags(la, 2, F0, pq);
       __builtin_amdgcn_sched_barrier(0);
@@ -616,6 +693,7 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
       read_frags(la, 1, F1, pq);
       read_frags(la, 2, F2, pq);
       mfma2(F0, F1);
+      mid();
       read_frags(la, 3, F3, pq);
       mfma2(F2, F3);
     }
@@ -674,7 +752,12 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
 #pragma unroll
       for (int w = 0; w < 3; ++w) issue_half(w, 1, slot0 ^ 1, cur);
     }
-    if (tid == 0) fetched = atomicAdd(next_ctr, 1);
+    // (opaque: for an address known to be the same in every lane the compiler
+    // combines the lanes' adds and waits for the result on the spot, which
+    // held the whole tile until its predecessor's stores were out: dW alone of
+    // the hidden-2048 block at 128 tokens 59 us, 51 without; with the SR update
+    // the wait is the faster form, 4-bit codes at 1531 tokens 116 against 125)
+    if (tid == 0) fetched = atomicAdd(next_ctr + (Epi::kSR ? 0 : opaque(0)), 1);
     if (g2) block_barrier();
     // (e4m3: a pair of sub-steps is one operand of eight registers)
     constexpr bool kF8 = ELEM == EF8 || ELEM == EF4B;
@@ -776,6 +859,8 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
     // against 5.06 ms).  STEADY: steps s + 1 and s + 2 exist and are whole.
     // (e4m3 B keeps it in the first phase: its eight-register operands would
     // be copied from one step to the next)
+    // Step 0 is in LDS as a whole when it begins: it waits for nothing in its
+    // first two phases, least of all for the last tile's stores.
     constexpr bool kEarlyB = ELEM != EF8;
     HB B0;
     if constexpr (kEarlyB) read_b(stage_ptr(slot0) + OPB, 0, B0);
@@ -798,8 +883,8 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
       if constexpr (!kEarlyB) read_b(lb, 0, B0);
       if (f1) {
         copies(3, s + 1, slot ^ 1);
-        wait_vm<6 + 2 * CB>();
-      } else {
+        if (s > 0) wait_vm<6 + 2 * CB>();
+      } else if (s > 0) {
         wait_vm<2>();
         if (ztail) zero_half(2, s, slot, cur);
       }
@@ -807,10 +892,10 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
       read_b(lb, 1, B1);
       if (f2) {
         copies(0, s + 2, slot);
-        wait_vm<6 + 2 * CB>();
+        if (s > 0) wait_vm<6 + 2 * CB>();
       } else if (f1) {
-        wait_vm<4 + 2 * CB>();
-      } else {
+        if (s > 0) wait_vm<4 + 2 * CB>();
+      } else if (s > 0) {
         wait_vm<0>();
         if (ztail) zero_half(3, s, slot, cur);
       }
@@ -871,10 +956,15 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
         }
         if (cur.tail && it == cur.nsteps - 1) zero_tail(it, slot, cur);
         block_barrier();                 // stage `slot` complete; step it - 1's stage is free
-        if (it + NS - 1 < cur.nsteps) issue(it + NS - 1, (slot + NS - 1) % NS, cur);
+        // int8: one of the two waves of each SIMD copies after its first group
+        // of MFMAs
+        const bool copy_now = ELEM != EI8 || wave_u < NW / 2;
+        if (copy_now && it + NS - 1 < cur.nsteps) issue(it + NS - 1, (slot + NS - 1) % NS, cur);
         // fetch the next tile early; its value is needed only at the epilogue
-        if (it == 0 && tid == 0) fetched = atomicAdd(next_ctr, 1);
-        compute(slot);
+        if (it == 0 && tid == 0) fetched = atomicAdd(next_ctr + opaque(0), 1);
+        compute(slot, [&]() {
+          if (!copy_now && it + NS - 1 < cur.nsteps) issue(it + NS - 1, (slot + NS - 1) % NS, cur);
+        });
       }
     }
 
@@ -886,7 +976,8 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
     const int bz = cur.bz;
     const int last = (slot0 + cur.nsteps + NS - 1) % NS;   // stage of the last step (staging area)
     if constexpr (Epi::kRowScale) {
-      if (tid < TILE) row_scale[tid] = epi.scale_fin(my_scale);
+      const int tid_e = opaque(tid);
+      if (tid_e < TILE) row_scale[tid_e] = epi.scale_fin(my_scale);
     }
     // SR epilogue: this lane's code chunks, rows sr_r + 16 u of each 32-row
     // block and columns 8 sr_c .. 8 sr_c + 7 of each 32-column block (8
@@ -1139,12 +1230,12 @@ __device__ __forceinline__ void gemm_v3_body(const Group<Epi>& grp, lds_u8* smem
   }
 }
 
-template <int ELEM, int MA, int MB, class Epi>
+template <int ELEM, int MA, int MB, class Epi, bool ONE>
 __global__ __launch_bounds__(NTH) void gemm_v3_kernel(const Group<Epi> grp) {
-  __shared__ __attribute__((aligned(1024))) uint8_t stages[StageGeo<MB>::kBytes];
+  __shared__ __attribute__((aligned(1024))) uint8_t stages[StageGeo<MB, ONE>::kBytes];
   __shared__ float row_scale[TILE];
   __shared__ int next_tile;
-  gemm_v3_body<ELEM, MA, MB, Epi>(grp, (lds_u8*)stages, (lds_f32*)row_scale, (lds_i32*)&next_tile);
+  gemm_v3_body<ELEM, MA, MB, Epi, ONE>(grp, (lds_u8*)stages, (lds_f32*)row_scale, (lds_i32*)&next_tile);
 }
 
 // Two groups of bf16 products in one launch: every block takes tiles of the
@@ -1152,8 +1243,8 @@ __global__ __launch_bounds__(NTH) void gemm_v3_kernel(const Group<Epi> grp) {
 // left without a tile of the first start on the second at once.
 template <int MA1, int MB1, class Epi1, int MA2, int MB2, class Epi2>
 __global__ __launch_bounds__(NTH) void gemm_v3_dual_kernel(const Group<Epi1> g1, const Group<Epi2> g2) {
-  static_assert(StageGeo<MB1>::kBytes == StageGeo<MB2>::kBytes, "one stage area");
-  __shared__ __attribute__((aligned(1024))) uint8_t stages[StageGeo<MB1>::kBytes];
+  static_assert(StageGeo<MB1, false>::kBytes == StageGeo<MB2, false>::kBytes, "one stage area");
+  __shared__ __attribute__((aligned(1024))) uint8_t stages[StageGeo<MB1, false>::kBytes];
   __shared__ float row_scale[TILE];
   __shared__ int next_tile;
   gemm_v3_body<EBF16, MA1, MB1, Epi1>(g1, (lds_u8*)stages, (lds_f32*)row_scale, (lds_i32*)&next_tile);
@@ -1662,7 +1753,7 @@ static void prep_group(Group<Epi>& grp, uint8_t* ws, int slot, XcdShares& sh) {
 
 // Persistent grid over one group: 8 x (blocks per XCD), one block per
 // compute unit at most.
-template <int ELEM, int MA, int MB, class Epi>
+template <int ELEM, int MA, int MB, class Epi, bool ONE = MB == KCP>
 static hipError_t launch_group(Group<Epi>& grp, uint8_t* ws, hipStream_t s, bool cleared) {
   XcdShares sh(group_tiles(grp));
   if (sh.total == 0) return hipSuccess;
@@ -1671,7 +1762,7 @@ static hipError_t launch_group(Group<Epi>& grp, uint8_t* ws, hipStream_t s, bool
   LaunchStatus st;
   if (!cleared) st << launch_kernel(sched_clear_kernel, dim3(1), dim3(64), s, reinterpret_cast<int*>(ws));
   st << timed_launch(s, [&] {
-    return launch_kernel(gemm_v3_kernel<ELEM, MA, MB, Epi>, dim3((unsigned)(8 * bpx)), dim3(NTH), s, grp);
+    return launch_kernel(gemm_v3_kernel<ELEM, MA, MB, Epi, ONE>, dim3((unsigned)(8 * bpx)), dim3(NTH), s, grp);
   });
   return st.e;
 }
@@ -1763,6 +1854,24 @@ size_t fwd_batch_workspace(int n, const LinearIO* io, int cf, size_t* offs) {
 size_t fwd_batch_workspace_min(int n, const LinearIO* io, int cf) {
   if (cf == CF_T2 && fwd_packed(n, io)) return kSchedBytes;
   return fwd_batch_workspace(n, io, cf, nullptr);
+}
+
+// The two-phase loop's steps are shorter, but its tiles start and end slower
+// (the first step's copies and its eight barriers have nothing to overlap
+// with), and a ragged last step costs it more: with few steps a tile the
+// one-phase loop is ahead.  The persistent GEMM with the one-phase loop alone
+// -> with two phases alone -> by this rule, us, blocks of 8192 tokens: hidden
+// 256 4-bit e4m3 32.1 -> 37.6 -> 32.0, 768 4-bit e4m3 81.4 -> 93.3 -> 81.6, 1344
+// (ragged) 4-bit int8 230 -> 242 -> 229, 1536 8-bit 258 -> 250 -> 250 (one phase:
+// 264).  Both loops give the same bits.
+static bool one_phase(const BatchCfg& c, const LinearIO* io) {
+  int64_t tiles = 0, steps = 0;
+  for (int l = 0; l < c.n; ++l) {
+    const int64_t t = ((c.M + TILE - 1) / TILE) * ((io[l].d_out + TILE - 1) / TILE);
+    tiles += t;
+    steps += t * ((io[l].d_in + KB - 1) / KB - (io[l].d_in % KB != 0 ? 5 : 0));
+  }
+  return 2 * steps < (c.act_e4m3 ? 22 : 17) * tiles;
 }
 
 hipError_t launch_fwd_batch(const BatchCfg& c, const LinearIO* io, uint8_t* ws, size_t ws_bytes,
@@ -1870,10 +1979,13 @@ hipError_t launch_fwd_batch(const BatchCfg& c, const LinearIO* io, uint8_t* ws, 
   if (packed) {
     if (c.act_e4m3) st << launch_group<EF4B, KC, KCP>(grp, ws, stream, false);
     else st << launch_group<EI8, KC, KCP>(grp, ws, stream, false);
-  } else if (fp4) {
-    st << launch_group<EF4B, KC, KF4>(grp, ws, stream, true);
+  } else if (one_phase(c, io)) {
+    if (fp4) st << launch_group<EF4B, KC, KF4, EpiFwd, true>(grp, ws, stream, true);
+    else if (c.act_e4m3) st << launch_group<EF8, KC, KC, EpiFwd, true>(grp, ws, stream, unpacked);
+    else st << launch_group<EI8, KC, KC, EpiFwd, true>(grp, ws, stream, unpacked);
   } else {
-    if (c.act_e4m3) st << launch_group<EF8, KC, KC>(grp, ws, stream, unpacked);
+    if (fp4) st << launch_group<EF4B, KC, KF4>(grp, ws, stream, true);
+    else if (c.act_e4m3) st << launch_group<EF8, KC, KC>(grp, ws, stream, unpacked);
     else st << launch_group<EI8, KC, KC>(grp, ws, stream, unpacked);
   }
   return st.e;
@@ -1895,8 +2007,10 @@ BwdPlan plan_bwd_batch(int n, const LinearIO* io, int64_t M) {
   P.splits = 1;
   P.splits_dual = 1;
   const int cus = current_device_cus();
-  // a step of a 256 x 256 bf16 tile is ~2048 MFMA cycles at ~2.1 GHz, plus
-  // ~2 us of per-tile prologue / epilogue; partials move at ~4 TB/s
+  // a step of a 256 x 256 bf16 tile is 2048 MFMA cycles, at ~2.1 GHz, plus ~2
+  // us of per-tile prologue / epilogue; partials move at ~4 TB/s.  (A lower
+  // bound since the power limit counts: full launches take about 1.6 us a step
+  // and 12 us for the end of an SR tile.)
   constexpr double kStepUs = 2048.0 / 2100.0, kTileUs = 2.0;
   auto tiles_of = [](int64_t I, int64_t J) { return ((I + TILE - 1) / TILE) * ((J + TILE - 1) / TILE); };
   double dx_us = 0;     // dX work of the whole batch, summed over its tiles
@@ -1925,8 +2039,8 @@ BwdPlan plan_bwd_batch(int n, const LinearIO* io, int64_t M) {
   // The SR update in the dW epilogue saves dW's store and a streaming pass
   // over it, at the price of ~173 vector instructions per 8 weights in the
   // dW tiles.  Measured per call it is the faster form on every LLaMA block
-  // (hidden 768, where those tiles are the launch's critical path: 288 us
-  // against 300 us staged), so it is the default; DQT_SR_EPILOGUE=staged in
+  // (hidden 768, where those tiles are the launch's critical path: 265 us
+  // against 256 us of products and 12 us of update), so it is the default; DQT_SR_EPILOGUE=staged in
   // the environment stages dW in the workspace and updates it in a pass of
   // its own (same dW bits, same codes), e.g. to test both forms.
   bool fuse = true;

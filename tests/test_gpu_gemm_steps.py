@@ -1,8 +1,8 @@
-"""The persistent GEMM's main loop at the ends of its reduction: one to five
-steps, whole and ragged (the loop keeps five half-tiles of copies in flight
-and drains them over its last two or three steps), for every operand layout:
-int8, e4m3 and FP4 forward, dX (K-contiguous), dW (K-major) unfused and with
-the SR update.  Rows and columns past one tile, ragged in both directions.
+"""The persistent GEMM's main loops at the ends of their reduction: one to five
+steps, whole and ragged (the two-phase loop keeps five half-tiles of copies in
+flight and drains them over its last two or three steps; forward tiles of few
+steps take the one-phase loop), for every operand layout: int8, e4m3 and FP4
+forward, dX (K-contiguous), dW (K-major) unfused and with the SR update.  Rows and columns past one tile, ragged in both directions.
 int8 is exact; the rest is bounded by fp32 sums of exact products, 1e-3 of
 sum |terms|, as every product of the library."""
 import numpy as np
@@ -49,8 +49,26 @@ def _forward(wfmt, act, M, d_out, d_in):
     alpha = np.float32(0.017)
     G.log(f"fwd {wfmt} {act} M={M} {d_in}->{d_out}")
     Xd, Xv = G.to_dev(X, "bf16")
-    _, _, Y = G.run_fwd(G.make_weight(d_out, d_in, wfmt, lo, hi, alpha), G.weight_codes_dev(q, wfmt), Xd, act, "f32")
+    w, Wq = G.make_weight(d_out, d_in, wfmt, lo, hi, alpha), G.weight_codes_dev(q, wfmt)
+    Xq, xdq, Y = G.run_fwd(w, Wq, Xd, act, "f32")
     torch.cuda.synchronize()
+    # beside a linear of 32 steps, whose mean takes the call to the two-phase
+    # loop: the same bits
+    K, N = 4096, max(272, d_out)
+    g = torch.Generator(device=G.DEV)
+    g.manual_seed(5)
+    Wl = torch.randint(0, 127, (N * K // (4 if wfmt == "ternary" else 1),), generator=g, device=G.DEV, dtype=torch.uint8)
+    if wfmt == "ternary":
+        Wl &= 0x55                              # codes 0 and 1
+    Xl = torch.randint(0, 127, (M, K), generator=g, device=G.DEV, dtype=torch.uint8)
+    wl = G.make_weight(N, K, wfmt, lo, hi, alpha, 1)
+    Y2 = torch.full_like(Y, -7.0)
+    io = dqt.linear_io([dict(w=w, Wq=Wq, Xq=Xq, xdq=xdq, Y=Y2),
+                        dict(w=wl, Wq=Wl, Xq=Xl, xdq=xdq, Y=torch.empty((M, N), device=G.DEV))])
+    dqt.dqt_linear_fwd_batch(io, M, G.act_code(act), dqt.DQT_F32,
+                             dqt.workspace(dqt.dqt_linear_fwd_batch_workspace(io)))
+    torch.cuda.synchronize()
+    assert torch.equal(Y2, Y)
     codes, d = O.act_quant(Xv, act)
     a = codes.astype(np.float64) if act == "i8" else O.e4m3_decode(codes).astype(np.float64)
     sc = (d.astype(np.float32) * alpha).astype(np.float32)[:, None]
