@@ -168,7 +168,8 @@ constexpr int64_t kMidSplitM = 256;
 constexpr int64_t kMidMaxE4M3 = 800;    // tokens
 constexpr int64_t kMidMaxTiles = 512;   // 256 x 256 output tiles of the batch
 constexpr int64_t kMidMaxTiles8 = 384;  // ... with 8-bit codes
-bool fwd_small_applies(const BatchCfg& c, const LinearIO* io);
+// packed: the persistent GEMM would run from the packed codes
+bool fwd_small_applies(const BatchCfg& c, const LinearIO* io, bool packed);
 hipError_t launch_fwd_small(const BatchCfg& c, const LinearIO* io, hipStream_t stream);
 BwdPlan plan_bwd_batch(int n, const LinearIO* io, int64_t M);
 hipError_t launch_dx_batch(const BatchCfg& c, const LinearIO* io, uint8_t* ws, const BwdPlan& P,

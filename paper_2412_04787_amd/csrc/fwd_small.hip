@@ -18,6 +18,8 @@
 //   h2048 8-bit, int8      72 -> 15   73 -> 22   74 -> 34   75 -> 37   77 -> 47   106 -> 73
 //   h768 ternary, int8     40 -> 14   40 -> 15   41 -> 18   41 -> 19   41 -> 24    43 -> 25
 // (14 us is two launches from the Python binding.)
+#include <algorithm>
+
 #include "gemm_common.h"
 #include "sr_rule.h"
 
@@ -615,23 +617,86 @@ hipError_t launch_small(SmallTab& tab, bool vec, hipStream_t stream) {
 // 32 us, h768 13 and 16 us; h4096 4-bit 61 and 55 us); with 8-bit codes
 // at 48 (h2048 29 and 31 us), or 16 where the launch has so many rows that
 // the mid kernel fills the chip (h4096: 16 tokens 73 and 70 us, 24 tokens 93
-// and 71 us).  The
-// mid kernel meets the persistent GEMM where that one's tiles fill the
-// compute units twice: with int8 activations at about 512 of its 256 x 256
-// tiles (h2048 4-bit: 504 tiles 128 against 137 us, 672 tiles 171 against
-// 147 us; h768: 372 tiles 53 against 63 us), or 384 with 8-bit codes, which
-// it does not have to expand (336 tiles 85 against 108 us, 504 tiles 128
-// against 122 us).  With e4m3 activations the fp32 sums of the two kernels
-// round differently, and a batch gives the results of its linears one by
-// one: there the rule is on the tokens alone (h4096: 777 tokens 207 against
-// 217 us, 1024 tokens 249 against 223 us).
+// and 71 us).
+// Above, the persistent GEMM's tile takes a step in half the time that four
+// tiles of the mid kernel need, but there are a quarter as many of them to
+// fill the compute units with, and its codes are expanded first.  Which of
+// the two is ahead turns on how full the last round of tiles is (one 4096 ->
+// 4096 linear, 8-bit codes: 777 tokens, 64 tiles, 48 against 25 us; 4096
+// tokens, 256 tiles, 65 against 91 us), so both are estimated: rounds of tiles
+// whose steps slow down as the compute units fill up (bandwidth and clock),
+// with constants fitted to 1800 calls of both (one linear to whole blocks,
+// d_in 16 to 65536, 65 to 4096 tokens, all formats).  Over those calls the
+// choice is at most 3 % slower than the persistent GEMM, and 0.1 % slower than
+// the better one on average; limits in tiles or tokens alone were up to 1.7
+// times slower where the GEMM's rounds are full.
+// The estimates stop where the mid kernel never wins by much: 512 of the 256 x
+// 256 tiles (384 with 8-bit codes), 800 tokens with e4m3 activations.
+// With e4m3 activations the fp32 sums come out the same on either side above
+// kMidSplitM tokens (both add 64 products per instruction, in the same order),
+// and a batch gives the results of its linears one by one; the reduction in
+// two halves, and the packed form that the persistent GEMM takes without a
+// workspace for the expansion, round differently: there the rule is on the
+// tokens alone.
 static bool codes8(const BatchCfg& c) { return !c.w_ternary && !c.w_int4 && !c.w_int3; }
-bool fwd_small_applies(const BatchCfg& c, const LinearIO* io) {
+
+// us of n tiles in rounds of `slots`: a tile of `steps` takes steps * step *
+// (1 + fill * share of the slots taken) + tile, in a round at most half full
+// `half` of that; at least as long as the longest tile.
+struct TileTime {
+  double step, tile, fill, half;
+  double round(double steps, double share) const {
+    return (steps * step * (1 + fill * share) + tile) * (share <= 0.5 ? half : 1.0);
+  }
+  double us(int64_t n, int64_t sum_steps, int64_t longest, int64_t slots) const {
+    const double mean = (double)sum_steps / (double)n;
+    const int64_t rem = n % slots;
+    const double t = (double)(n / slots) * round(mean, 1.0) + (rem > 0 ? round(mean, (double)rem / (double)slots) : 0.0);
+    return std::max(t, round((double)longest, n < slots ? (double)n / (double)slots : 1.0));
+  }
+};
+
+static bool mid_is_ahead(const BatchCfg& c, const LinearIO* io) {
+  const int64_t cus = current_device_cus();
+  const bool split = c.M <= kMidSplitM;
+  bool fp4 = c.w_ternary && c.act_e4m3;
+  for (int l = 0; l < c.n; ++l) fp4 &= io[l].d_in % 64 == 0;
+  int64_t np = 0, sp = 0, lp = 0, nm = 0, sm = 0, lm = 0;
+  double weights = 0;
+  for (int l = 0; l < c.n; ++l) {
+    const int64_t k = io[l].d_in, n = io[l].d_out;
+    const int64_t tp = ((c.M + 255) / 256) * ((n + 255) / 256), kp = (k + 127) / 128;
+    const int64_t tm = ((c.M + MTI - 1) / MTI) * ((n + MTI - 1) / MTI), km = split ? (k + 255) / 256 : kp;
+    np += tp;
+    sp += tp * kp;
+    lp = std::max(lp, kp);
+    nm += tm;
+    sm += tm * km;
+    lm = std::max(lm, km);
+    weights += (double)(k * n);
+  }
+  // the persistent GEMM, after the pass that expands its codes (4.4 TB/s)
+  double big = 7.6 + TileTime{!c.act_e4m3 ? 1.1 : fp4 ? 0.93 : 1.21, 3.4, 0.41, 1.0}.us(np, sp, lp, cus);
+  if (!codes8(c)) big += 3.7 + weights * ((c.w_ternary ? 0.25 : c.w_int4 ? 0.5 : 0.375) + (fp4 ? 0.5 : 1.0)) / 4.4e6;
+  const double fmt = c.w_ternary ? 0.93 : c.w_int4 ? 1.08 : c.w_int3 ? 1.22 : 1.0;
+  const TileTime mid = split ? TileTime{0.87 * fmt, 3.1, 0.46, 1.0} : TileTime{0.78 * fmt, 3.25, 0.46, 0.69};
+  return 1.02 * (3.4 + mid.us(nm, sm, lm, split ? cus : 2 * cus)) <= big;
+}
+
+bool fwd_small_applies(const BatchCfg& c, const LinearIO* io, bool packed) {
   if (c.M <= kSkinnyM) return true;
-  if (c.act_e4m3) return c.M <= kMidMaxE4M3;
-  int64_t tiles = 0;
-  for (int l = 0; l < c.n; ++l) tiles += ((c.M + 255) / 256) * ((io[l].d_out + 255) / 256);
-  return tiles <= (codes8(c) ? kMidMaxTiles8 : kMidMaxTiles);
+  if (c.act_e4m3) {
+    if (c.M > kMidMaxE4M3) return false;
+    // (the second half of a reduction of at most 128 elements is empty)
+    bool halves = false;
+    for (int l = 0; l < c.n; ++l) halves |= c.M <= kMidSplitM && io[l].d_in > 128;
+    if (packed || halves) return true;
+  } else {
+    int64_t tiles = 0;
+    for (int l = 0; l < c.n; ++l) tiles += ((c.M + 255) / 256) * ((io[l].d_out + 255) / 256);
+    if (tiles > (codes8(c) ? kMidMaxTiles8 : kMidMaxTiles)) return false;
+  }
+  return mid_is_ahead(c, io);
 }
 
 hipError_t launch_fwd_small(const BatchCfg& c, const LinearIO* io, hipStream_t stream) {

@@ -1877,7 +1877,6 @@ static bool one_phase(const BatchCfg& c, const LinearIO* io) {
 hipError_t launch_fwd_batch(const BatchCfg& c, const LinearIO* io, uint8_t* ws, size_t ws_bytes,
                            hipStream_t stream) {
   if (c.M == 0 || c.n == 0) return hipSuccess;
-  if (fwd_small_applies(c, io)) return launch_fwd_small(c, io, stream);
   LaunchStatus st;
   size_t offs[kMaxBatch];
   const size_t full =
@@ -1886,6 +1885,7 @@ hipError_t launch_fwd_batch(const BatchCfg& c, const LinearIO* io, uint8_t* ws, 
   // ternary codes straight from the packed form only when the workspace
   // cannot hold their expansion
   const bool packed = aligned && ws_bytes < full;
+  if (fwd_small_applies(c, io, packed)) return launch_fwd_small(c, io, stream);
   // FP4 values of ternary codes in the workspace (e4m3 activations)
   const bool fp4 = aligned && !packed && c.act_e4m3;
   // int8 (or e4m3) copy of the codes in the workspace
@@ -2040,9 +2040,10 @@ BwdPlan plan_bwd_batch(int n, const LinearIO* io, int64_t M) {
   // over it, at the price of ~173 vector instructions per 8 weights in the
   // dW tiles.  Measured per call it is the faster form on every LLaMA block
   // (hidden 768, where those tiles are the launch's critical path: 265 us
-  // against 256 us of products and 12 us of update), so it is the default; DQT_SR_EPILOGUE=staged in
-  // the environment stages dW in the workspace and updates it in a pass of
-  // its own (same dW bits, same codes), e.g. to test both forms.
+  // against 256 us of products and 12 us of update), so it is the default;
+  // DQT_SR_EPILOGUE=staged in the environment stages dW in the workspace and
+  // updates it in a pass of its own (same dW bits, same codes), e.g. to test
+  // both forms.
   bool fuse = true;
   if (const char* f = getenv("DQT_SR_EPILOGUE")) fuse = strcmp(f, "staged") != 0;
   P.sr_fused = P.splits == 1 && fuse;

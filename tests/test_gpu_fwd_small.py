@@ -89,3 +89,44 @@ def test_batch_equals_singles_and_needs_only_the_counters(M):
     for e, Y in zip(ents, singles):
         assert torch.equal(e["Y"][:Y.numel()].view_as(Y), Y)
         assert bool((e["Y"][Y.numel():] == -7.0).all())
+
+
+# (M, wfmt, act, shapes): the first linear alone fills its rounds of tiles and
+# takes the persistent GEMM (on FP4, e4m3 and int8 operands); the others alone
+# take the 128 x 128 tiles, as does the batch with e4m3 activations, at 200 and
+# 256 tokens with the reduction in two halves
+ACROSS = [(800, "ternary", "e4m3", [(576, 32768), (704, 1040), (64, 48)]),
+          (800, "i3", "e4m3", [(576, 32768), (272, 1040), (1040, 144)]),
+          (800, "i8", "i8", [(1024, 32768), (272, 1040), (1040, 144)]),
+          (200, "ternary", "e4m3", [(64, 65536), (192, 272)]),
+          (256, "i4", "e4m3", [(16, 65536), (272, 16)])]
+
+
+@pytest.mark.parametrize("M,wfmt,act,shapes", ACROSS)
+def test_batch_is_its_singles_across_the_line(M, wfmt, act, shapes):
+    """fp32 outputs, bit for bit, of inputs whose products span 12 powers of
+    two; also with the 256 counter bytes alone, where the formats allow it."""
+    g = torch.Generator(device=G.DEV)
+    g.manual_seed(M + len(wfmt))
+    lo, hi = GRID[wfmt]
+    ents, singles = [], []
+    for tid, (d_in, d_out) in enumerate(shapes):
+        G.log(f"across the line M={M} {d_in}->{d_out} {wfmt} {act}")
+        q = np.random.default_rng(tid).integers(lo, hi + 1, size=(d_out, d_in)).astype(np.int8)
+        w = G.make_weight(d_out, d_in, wfmt, lo, hi, 0.02, tid)
+        Wq = G.weight_codes_dev(q, wfmt)
+        X = torch.randn((M, d_in), generator=g, device=G.DEV)
+        X *= torch.exp2(torch.randint(-6, 7, (M, d_in), generator=g, device=G.DEV).float())
+        Xq, xdq, Y = G.run_fwd(w, Wq, X, act, "f32")
+        ents.append(dict(w=w, Wq=Wq, Xq=Xq, xdq=xdq, Y=torch.full_like(Y, -7.0)))
+        singles.append(Y)
+    io = dqt.linear_io(ents)
+    sizes = [dqt.dqt_linear_fwd_batch_workspace(io)]
+    if wfmt == "ternary":
+        sizes.append(256)
+    for nbytes in sizes:
+        dqt.dqt_linear_fwd_batch(io, M, G.act_code(act), dqt.DQT_F32, dqt.workspace(nbytes))
+        torch.cuda.synchronize()
+        for e, Y in zip(ents, singles):
+            assert torch.equal(e["Y"], Y)
+            e["Y"].fill_(-7.0)
