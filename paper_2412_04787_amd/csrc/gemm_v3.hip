@@ -21,7 +21,7 @@
 //    of a SIMD run half a phase apart, so one's memory part always runs
 //    beside the other's matrix instructions, and five half-tiles of copies
 //    stay in flight.  Bound by the board's power: the matrix cores are busy
-//    79 % of the cycles (60 % with all waves in the same phase and the copies
+//    77 % of the cycles (60 % with all waves in the same phase and the copies
 //    in one burst per step), and the clock falls from 1.87 to about 1.6 GHz
 //    under it.  Measured, that form -> this: hidden-4096 backward + SR 5.85
 //    -> 5.06 ms (1310 TFLOP/s), hidden-2048 3.05 -> 2.70 ms, hidden-768 282
@@ -1780,18 +1780,24 @@ static hipError_t launch_dual(Group<Epi1>& g1, Group<Epi2>& g2, uint8_t* ws, hip
   // The group with the longest tile goes first, so that the launch ends on
   // short tiles: with few tokens dX's tiles (reduction d_out) are longer than
   // dW's (reduction M), and left to the end they ran with most compute units
-  // idle (backward + SR, with the merged pre-pass: hidden-2496 block, 237
-  // tokens 370 -> 230 us; hidden-2048, 256 tokens 214 -> 147 us; hidden-768,
-  // 512 tokens 86 -> 61 us).  Over many rounds of tiles the end matters
+  // idle (backward + SR: hidden-2496 block, 237 tokens 370 -> 230 us;
+  // hidden-2048, 256 tokens 214 -> 147 us; hidden-768, 512 tokens 86 -> 61 us).
+  // dX goes first only where its longest tile is 1.5 times dW's, whose SR update
+  // counts like 8 steps: dX's other tiles are shorter, and closer to the line
+  // they and the update's end cost more (hidden 640, 1562 tokens 79 us with dW
+  // first, 117 with dX; hidden 768, 2048 tokens 95 and 132; hidden 2048, 1280
+  // tokens 352 and 319; of 339 calls none is slower by this rule than with dW
+  // first on the one-phase loop).  Over many rounds of tiles the end matters
   // little, and dW first is the better neighbour for the caches (hidden-4096,
   // 8192 tokens, 29 rounds: 5.09 against 5.14 ms; 1024 tokens, 14 rounds: 907
   // against 889 us).  Each order is a kernel of its own: one kernel with the
   // order as an argument spilled more and was 1-2 % slower on large blocks.
   constexpr int64_t kOrderRounds = 16;
+  constexpr int64_t kSrTile = Epi1::kSR ? 8 * (KB / 2) : 0;
   auto longest = [](const auto& g) { return g.ng > 0 ? std::min(g.p[0].split_len, g.p[0].R) : 0; };
   const dim3 grid((unsigned)(8 * bpx));
   st << timed_launch(s, [&] {
-    if (longest(g2) > longest(g1) && sh.total <= kOrderRounds * 8 * bpx)
+    if (2 * longest(g2) > 3 * longest(g1) + 2 * kSrTile && sh.total <= kOrderRounds * 8 * bpx)
       return launch_kernel(gemm_v3_dual_kernel<MA2, MB2, Epi2, MA1, MB1, Epi1>, grid, dim3(NTH), s, g2, g1);
     return launch_kernel(gemm_v3_dual_kernel<MA1, MB1, Epi1, MA2, MB2, Epi2>, grid, dim3(NTH), s, g1, g2);
   });
