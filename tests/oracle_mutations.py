@@ -44,7 +44,9 @@ MUT = [
 src = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 tmp = tempfile.mkdtemp()
 dst = os.path.join(tmp, "r")
-shutil.copytree(src, dst, ignore=shutil.ignore_patterns(".git", "_work", "gpurun_out", "__pycache__", "_build"))
+for f in subprocess.check_output(["git", "ls-files"], cwd=src, text=True).splitlines():
+    os.makedirs(os.path.dirname(os.path.join(dst, f)), exist_ok=True)
+    shutil.copy(os.path.join(src, f), os.path.join(dst, f))
 orig = open(os.path.join(dst, "oracle/dqt_oracle.py")).read()
 tests = sorted(f"tests/{f}" for f in os.listdir(os.path.join(dst, "tests")) if f.startswith("test_oracle") or f == "test_model_cpu.py")
 survived = 0
